@@ -38,6 +38,9 @@ __device__ __forceinline__ void gstore(gptr<V> p, const V &v) {
   *(gptr<typename V::Native_vec_>)p = get_native_vector(v);
 }
 
+// v mod M for -M <= v < 2M (an index next to a periodic grid): no division.
+__device__ __forceinline__ int wrap_once(int v, int M) { return v < 0 ? v + M : (v >= M ? v - M : v); }
+
 __device__ inline int mod_pos(int a, int m) {
   int r = a % m;
   return r < 0 ? r + m : r;
@@ -52,6 +55,15 @@ __device__ inline int mesh_cell(double x, double m_over_l, int M, double *t) {
   c = c < 0 ? 0 : (c > M - 1 ? M - 1 : c);
   *t = tt;
   return c;
+}
+
+// Real-space cell of a wrapped position (x < L can still round to ncell).
+__device__ inline int cell_of(double x, double y, double z, const CellParams &cp) {
+  int cx = (int)(x * cp.inv_cell), cy = (int)(y * cp.inv_cell), cz = (int)(z * cp.inv_cell);
+  cx = cx < cp.ncell ? cx : cp.ncell - 1;
+  cy = cy < cp.ncell ? cy : cp.ncell - 1;
+  cz = cz < cp.ncell ? cz : cp.ncell - 1;
+  return (cx * cp.ncell + cy) * cp.ncell + cz;
 }
 
 // q = a / b and *rem = a % b for 0 <= a < 2^22 and 1 <= b < 2^11, from a
@@ -70,6 +82,13 @@ __device__ __forceinline__ int fdivmod(int a, int b, float inv_b, int *rem) {
   }
   *rem = r;
   return q;
+}
+
+// The same for any a >= 0 and b >= 1, by integer division beyond that range.
+__device__ __forceinline__ int divmod(int a, int b, int *rem) {
+  if (a < (1 << 22) && b < (1 << 11)) return fdivmod(a, b, 1.0f / (float)b, rem);
+  *rem = a % b;
+  return a / b;
 }
 
 // ---------------------------------------------------------------------------
@@ -107,6 +126,11 @@ __device__ __forceinline__ void clenshaw_n(const T *const (&c)[NS], const T (&x)
   for (int i = 0; i < NS; ++i) out[i] = c[i][0] + x[i] * b1[i] - b2[i];
 }
 
+// Set bits of a wavefront mask below the calling lane.
+__device__ __forceinline__ int lanes_below(unsigned long long mask) {
+  return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+}
+
 // ---------------------------------------------------------------------------
 // Wavefront reductions (butterfly over 64 lanes; every lane ends with the sum;
 // the order of additions is fixed, so results are reproducible).
@@ -115,6 +139,23 @@ template <typename T>
 __device__ inline T wave_sum(T v) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
+  return v;
+}
+
+// Sum over each row of 16 lanes, in every lane of the row (DPP rotations).
+__device__ __forceinline__ double row_sum(double v) {
+#define ENUF_ROW_ROR(n)                                                                                  \
+  {                                                                                                      \
+    const long long b = __double_as_longlong(v);                                                         \
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x120 + (n), 0xf, 0xf, true);                  \
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x120 + (n), 0xf, 0xf, true);          \
+    v += __longlong_as_double(((long long)hi << 32) | (unsigned)lo);                                     \
+  }
+  ENUF_ROW_ROR(8)
+  ENUF_ROW_ROR(4)
+  ENUF_ROW_ROR(2)
+  ENUF_ROW_ROR(1)
+#undef ENUF_ROW_ROR
   return v;
 }
 

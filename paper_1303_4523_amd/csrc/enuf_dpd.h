@@ -32,8 +32,10 @@ struct DpdCharges {
   int *slot = nullptr;          // plan: slot map read by the combine kernel
   int *ccnt = nullptr;          // plan: charge cell grid
   double4 *cgrid = nullptr;
-  float4 *cpre = nullptr;
+  int *cidx = nullptr;
   CellParams cells{};
+  unsigned long long *freal = nullptr, *ereal = nullptr;  // plan: real-space results (zeroed for charges
+                                                          // that a full cell has no slot for)
   int *xcnt = nullptr;          // plan: charges binned by mesh x-cell
   int *xslot = nullptr;
   int M = 0, xcap = 0;
@@ -52,7 +54,7 @@ struct BatchMember {
   int nq;                       // charged particles (static compaction)
   int nblk;                     // blocks of 256 particles (pre, combine)
   int pair_blocks;              // blocks of the pair kernel
-  int real_blocks;              // blocks of the real-space kernel (one wave per charge)
+  int real_blocks;              // blocks of the real-space kernel
   double fscale, inv2piL;       // M / (pi L^2), 1 / (2 pi L)
   int64_t N;
   DpdParams P;
@@ -96,7 +98,7 @@ hipError_t configure_pair_kernels(size_t lds_bytes);
 // Blocks of the pair kernel (one per column segment), a multiple of 8 (whole
 // rounds over the XCDs).
 int pair_blocks(const DpdParams &P);
-hipError_t launch_batch_real(const BatchMember *mem, const int2 *map, int nmap, hipStream_t st);
+hipError_t launch_batch_real(const BatchMember *mem, const int2 *map, int nmap, int energies, hipStream_t st);
 // pass_threads, x_threads: work-group sizes of the spread/gather passes and of
 // the x pass (at least fft_max_butterflies of every member).
 hipError_t launch_batch_recip(const BatchMember *mem, int precision, int ik, const int2 *fwd, int nfwd,

@@ -72,6 +72,13 @@ __device__ __forceinline__ void dpd_pre_scalars(const DpdCharges &ch, int64_t i)
     ch.sc->sum_q = ch.stat.sum_q;
     ch.sc->sum_absq = ch.stat.sum_absq;
     ch.sc->sum_q2 = ch.stat.sum_q2;
+    // (field by field: a copy of the struct put the kernel's arguments in memory)
+    ch.sc->split.seg = ch.stat.split.seg;
+    ch.sc->split.nseg = ch.stat.split.nseg;
+    ch.sc->split.shares = ch.stat.split.shares;
+    ch.sc->split.group = ch.stat.split.group;
+    ch.sc->split.items = ch.stat.split.items;
+    ch.sc->split.per_charge = ch.stat.split.per_charge;
   }
 }
 
@@ -116,12 +123,7 @@ dpd_pre_particle(int64_t i, int mode, const DpdParams &P, double *r, double *v, 
   // cells of a charge: real-space grid and mesh x-bin
   int c = 0, xc = 0;
   if (j >= 0) {
-    const CellParams &cp = ch.cells;
-    int cx = (int)(r[0] * cp.inv_cell), cy = (int)(r[1] * cp.inv_cell), cz = (int)(r[2] * cp.inv_cell);
-    cx = cx < cp.ncell ? cx : cp.ncell - 1;
-    cy = cy < cp.ncell ? cy : cp.ncell - 1;
-    cz = cz < cp.ncell ? cz : cp.ncell - 1;
-    c = (cx * cp.ncell + cy) * cp.ncell + cz;
+    c = cell_of(r[0], r[1], r[2], ch.cells);
     double t;
     xc = mesh_cell(r[0], ch.m_over_l, ch.M, &t) * kXSub + (j & (kXSub - 1));  // x-cell sub-bin
   }
@@ -146,9 +148,11 @@ dpd_pre_particle(int64_t i, int mode, const DpdParams &P, double *r, double *v, 
       const CellParams &cp = ch.cells;
       if (sl < cp.cap) {
         ch.cgrid[(size_t)c * cp.cap + sl] = make_double4(r[0], r[1], r[2], qi);
-        ch.cpre[(size_t)c * cp.cap + sl] = make_float4((float)r[0], (float)r[1], (float)r[2], __int_as_float(j));
-      } else {
+        ch.cidx[(size_t)c * cp.cap + sl] = j;
+      } else {  // not in the grid: no real-space force
         atomicCAS(&ch.sc->status, 0, kEOverflow);
+        for (int a = 0; a < 3; ++a) ch.freal[3 * (size_t)j + a] = 0ull;
+        for (int a = 0; a < 2; ++a) ch.ereal[2 * (size_t)j + a] = 0ull;
       }
       if (xs < ch.xcap)
         ch.xslot[(size_t)xc * ch.xcap + xs] = j;

@@ -28,6 +28,51 @@ constexpr int kBatchStage = 256;
 constexpr int kBatchXThreads = 128;
 constexpr int kMaxParts = 8;       // most work-groups per plane in the spread and gather passes
 
+// Real-space work split.  A block takes a segment of `seg` cells of a column,
+// or, where cells are full or the grid has few cells, one of the `shares` of a
+// cell's charges; at most kRealOwn charges at a time.  A single evaluation asks
+// for about kRealTargetBlocks blocks; a DPD step, where the pair kernel and the
+// mesh passes share the device, for kRealDpdBlocks (642 against 678 us per 11
+// steps at N = 3333, the same at N = 24000); batches, which fill the device,
+// for none.  Larger targets for one evaluation (1024, 2048) gained on 27 full
+// cells (98 -> 88 us) and lost on sparse ones (14.9 -> 17.7 us).
+constexpr int kRealOwn = 64;
+constexpr int kRealSegMax = 4;
+constexpr int kRealTargetBlocks = 512, kRealDpdBlocks = 216;
+constexpr int kRealFill = 336;   // staged candidates a segment may expect (of a stage of 384)
+struct RealSplit {
+  int seg, nseg, shares, group;
+  int items;        // blocks' worth of work
+  int per_charge;   // far fewer charges than cells: an item per charge
+};
+__host__ __device__ inline RealSplit real_split(int nq, int n, int blocks) {
+  RealSplit s;
+  const int n2 = n * n, n3 = n2 * n;
+  const int mean = nq / n3 + 1;  // charges per cell, rounded up
+  s.seg = 1;
+  while (n >= 3 && s.seg < kRealSegMax && s.seg < n && 9 * (s.seg + 3) * mean <= kRealFill &&
+         n2 * ((n + s.seg) / (s.seg + 1)) >= blocks)
+    ++s.seg;
+  s.nseg = (n + s.seg - 1) / s.seg;
+  s.shares = 1;
+  s.group = kRealOwn;
+  if (s.seg == 1) {
+    // room for the counts' spread: a share's charges beyond its group would
+    // be taken with the candidates staged again
+    int sd = 1;
+    while (sd * sd < mean) ++sd;
+    const int full = mean + 3 * sd;
+    const int most = (full + 3) / 4, fill = blocks / n3, need = (full + kRealOwn - 1) / kRealOwn;
+    s.shares = fill < most ? fill : most;
+    s.shares = s.shares > need ? s.shares : need;
+    s.group = ((full + s.shares - 1) / s.shares + 3) / 4 * 4;
+    s.group = s.group < kRealOwn ? s.group : kRealOwn;
+  }
+  s.per_charge = nq < n3 / 8;
+  s.items = s.per_charge ? nq : n2 * s.nseg * s.shares;
+  return s;
+}
+
 // Device-resident scalars produced by the preparation kernels of one compute.
 struct DevScalars {
   int nq;               // number of charged particles (compacted prefix of xq)
@@ -37,6 +82,7 @@ struct DevScalars {
   double sum_q;         // sum q, sum |q|, sum q^2 (fixed-order reductions)
   double sum_absq;
   double sum_q2;
+  RealSplit split;      // work split of the real-space kernel for these charges
 };
 
 // Mixed-radix factorisation of an FFT length, radices in {2, 3, 4, 5, 8}.
@@ -139,8 +185,7 @@ struct ComputeBuffers {
   // real-space cell grid
   int *ccnt;             // [2 ncell^3] two sets: a DPD step bins into one while the other is cleared
   double4 *cgrid;        // [ncell^3 * cap] (x, y, z, q) per cell slot
-  float4 *cpre;          // [ncell^3 * cap] FP32 (x, y, z) and the compact index (bits in w) per cell
-                         // slot: what the real-space scan's pre-test reads
+  int *cidx;             // [ncell^3 * cap] compact index per cell slot
   unsigned long long *freal;  // [N * 3] fixed-point real-space force per compact slot
   unsigned long long *ereal; // [2 N] fixed-point (E_real whole, E_slater) of the pairs (j, k > j), per compact slot j
   long long *blk_er;         // [2 nblk] per-block sums of ereal over the particles of the block
@@ -217,8 +262,12 @@ inline double combine_fscale(const ComputeConfig &cfg) {
 // one stream; the DPD step forks the real-space phase onto another stream).
 hipError_t launch_prep(const ComputeConfig &cfg, const ComputeBuffers &b, const double *pos,
                        const double *q, hipStream_t st, KernelTimer *tm);
-hipError_t launch_real(const ComputeConfig &cfg, const ComputeBuffers &b, int64_t nq_max, hipStream_t st,
-                       KernelTimer *tm);
+// Blocks of the real-space kernel for up to nq_max charges.
+int real_blocks(const CellParams &cp, int64_t nq_max, int blocks);
+// energies: also leave the charges' pair energies (a step whose energies no one
+// reads skips them).
+hipError_t launch_real(const ComputeConfig &cfg, const ComputeBuffers &b, int64_t nq_max, int energies,
+                       hipStream_t st, KernelTimer *tm);
 // x_threads: work-group size of the x pass (at least fft_max_butterflies of
 // the mesh, at most kPassThreads; others are raised or clamped to fit).
 hipError_t launch_recip(const ComputeConfig &cfg, const ComputeBuffers &b, int64_t nq_max, hipStream_t st,

@@ -470,7 +470,7 @@ std::array<size_t, kPlanBuffers> plan_buffer_bytes(int64_t N, int p, int M, int 
           n * sizeof(int),                                    // slot
           2 * ncell3 * sizeof(int),                           // ccnt (two sets)
           ncell3 * cap * sizeof(double4),                     // cgrid
-          ncell3 * cap * sizeof(float4),                      // cpre
+          ncell3 * cap * sizeof(int),                         // cidx
           n * 3 * sizeof(unsigned long long),                 // freal
           n * 2 * sizeof(unsigned long long),                 // ereal
           nblk * 2 * sizeof(long long),                       // blk_er
@@ -601,7 +601,7 @@ ComputeBuffers carve_buffers(void *const *ptr) {
   b.slot = (int *)ptr[5];
   b.ccnt = (int *)ptr[6];
   b.cgrid = (double4 *)ptr[7];
-  b.cpre = (float4 *)ptr[8];
+  b.cidx = (int *)ptr[8];
   b.freal = (unsigned long long *)ptr[9];
   b.ereal = (unsigned long long *)ptr[10];
   b.blk_er = (long long *)ptr[11];
@@ -842,7 +842,7 @@ static int compute_impl(enuf_plan *plan, const double *pos, const double *q, dou
     if (e == hipSuccess) e = hipEventRecord(plan->fork_ev, st);
     if (e == hipSuccess) e = launch_recip(c, plan->buf, c.N, st, nullptr);
     if (e == hipSuccess) e = hipStreamWaitEvent(plan->side, plan->fork_ev, 0);
-    if (e == hipSuccess) e = launch_real(c, plan->buf, c.N, plan->side, nullptr);
+    if (e == hipSuccess) e = launch_real(c, plan->buf, c.N, 1, plan->side, nullptr);
     if (e == hipSuccess) e = hipEventRecord(plan->join_ev, plan->side);
     if (e == hipSuccess) e = hipStreamWaitEvent(st, plan->join_ev, 0);
     if (e == hipSuccess) e = launch_combine(c, plan->buf, forces, energy, energy5, FinishArgs(), st, nullptr);
@@ -1295,8 +1295,10 @@ enuf_dpd *enuf_dpd_create(int64_t N, double box, const enuf_dpd_params *prm, enu
     ch.slot = plan->buf.slot;
     ch.ccnt = plan->buf.ccnt;
     ch.cgrid = plan->buf.cgrid;
-    ch.cpre = plan->buf.cpre;
+    ch.cidx = plan->buf.cidx;
     ch.cells = plan->cfg.cells;
+    ch.freal = plan->buf.freal;
+    ch.ereal = plan->buf.ereal;
     ch.xcnt = plan->buf.xcnt;
     ch.xslot = plan->buf.xslot;
     ch.M = plan->cfg.mesh.M;
@@ -1304,6 +1306,7 @@ enuf_dpd *enuf_dpd_create(int64_t N, double box, const enuf_dpd_params *prm, enu
     ch.m_over_l = plan->cfg.mesh.m_over_l;
     ch.sc = plan->buf.sc;
     ch.stat = st;
+    ch.stat.split = real_split(nq, plan->cfg.cells.ncell, kRealDpdBlocks);
   }
   if (hipStreamCreateWithFlags(&d->side, hipStreamNonBlocking) != hipSuccess ||
       hipEventCreateWithFlags(&d->join_ev, hipEventDisableTiming) != hipSuccess ||
@@ -1435,7 +1438,7 @@ static int dpd_eval(enuf_dpd *d, int mode, double *pos, double *vel, double *for
       e = launch_dpd_pair(N, d->P, step, pos, dcnt, d->cpos, d->cvel, d->bond_start, d->bond_to,
                           d->fdpd, s1, tm, step_dev);
     const int ndcell3 = d->P.ncell * d->P.ncell * d->P.ncell;
-    if (e == hipSuccess) e = launch_real(pl->cfg, bk, d->nq, s1, tm);
+    if (e == hipSuccess) e = launch_real(pl->cfg, bk, d->nq, energies ? 1 : 0, s1, tm);
     if (events && e == hipSuccess) e = hipEventRecord(d->join_ev, s1);
     if (events && e == hipSuccess) e = hipStreamWaitEvent(st, d->join_ev, 0);
     // the combine kernel depends on the mesh passes and the real-space term
@@ -1795,8 +1798,7 @@ BatchMember member_view(const enuf_batch::Member &mb, const enuf_batch::Tuning &
   m.buf = plan_buffers_set(pl, par);
   m.nq = (int)d->nq;
   m.nblk = pl->cfg.nblk;
-  const int64_t g = (d->nq + 3) / 4;
-  m.real_blocks = (int)(g < 1 ? 1 : (g < 2048 ? g : 2048));
+  m.real_blocks = real_blocks(pl->cfg.cells, d->nq, 0);
   m.fscale = pl->cfg.mesh.ik ? 2.0 / (pl->cfg.L * pl->cfg.L) : (double)pl->cfg.mesh.M / (M_PI * pl->cfg.L * pl->cfg.L);
   m.inv2piL = 1.0 / (2.0 * M_PI * pl->cfg.L);
   m.N = d->N;
@@ -1820,6 +1822,7 @@ BatchMember member_view(const enuf_batch::Member &mb, const enuf_batch::Tuning &
   m.status = d->status;
   m.ch = dpd_charges_set(d, par);
   m.ch_next = dpd_charges_set(d, par ^ 1);
+  m.ch.stat.split = m.ch_next.stat.split = real_split((int)d->nq, pl->cfg.cells.ncell, 0);
   m.step = d->step_ctr;
   return m;
 }
@@ -1911,8 +1914,9 @@ const BatchMember *batch_table(const enuf_batch *b, int par) { return b->dmem + 
 // The forces of one step of every member, after its pre kernel: pair forces
 // and real space forked onto two side streams (fork = true) or kept on the
 // batch stream, the mesh passes on the batch stream, joined before return.
-// tm (eager single-stream steps only) brackets one stage with events.
-hipError_t batch_forces(enuf_batch *b, const BatchMember *mt, bool fork, KernelTimer *tm) {
+// tm (eager single-stream steps only) brackets one stage with events;
+// energies: the step's pair energies are wanted.
+hipError_t batch_forces(enuf_batch *b, const BatchMember *mt, bool fork, int energies, KernelTimer *tm) {
   const int *o = b->off;
   const int2 *mp = b->dmap;
   hipStream_t st = b->own;
@@ -1927,7 +1931,7 @@ hipError_t batch_forces(enuf_batch *b, const BatchMember *mt, bool fork, KernelT
   if (tm) tm->after(ENUF_K_DPD_PAIR, s0);
   if (fork && e == hipSuccess) e = hipEventRecord(b->join_ev[0], s0);
   if (tm) tm->before(ENUF_K_REAL, s1);
-  if (e == hipSuccess) e = launch_batch_real(mt, mp + o[2], o[3] - o[2], s1);
+  if (e == hipSuccess) e = launch_batch_real(mt, mp + o[2], o[3] - o[2], energies, s1);
   if (tm) tm->after(ENUF_K_REAL, s1);
   if (fork && e == hipSuccess) e = hipEventRecord(b->join_ev[1], s1);
   if (e == hipSuccess)
@@ -1949,7 +1953,7 @@ hipError_t batch_step(enuf_batch *b, bool fork, KernelTimer *tm = nullptr) {
   if (tm) tm->before(ENUF_K_DPD_PRE, st);
   hipError_t e = launch_batch_pre(mt, mp + o[0], o[1] - o[0], 0, st);
   if (tm) tm->after(ENUF_K_DPD_PRE, st);
-  if (e == hipSuccess) e = batch_forces(b, mt, fork, tm);
+  if (e == hipSuccess) e = batch_forces(b, mt, fork, 1, tm);
   if (tm) tm->before(ENUF_K_COMBINE, st);
   if (e == hipSuccess) e = launch_batch_combine(mt, b->nmem, mp + o[6], o[7] - o[6], 0, st);
   if (tm) tm->after(ENUF_K_COMBINE, st);
@@ -1966,7 +1970,7 @@ int batch_capture(enuf_batch *b, int kind, int par) {
   const int2 *mp = b->dmap;
   const BatchMember *mt = batch_table(b, par);
   HIP_OR_RETURN(hipStreamBeginCapture(b->own, hipStreamCaptureModeThreadLocal), ENUF_EDEVICE);
-  hipError_t e = batch_forces(b, mt, false, nullptr);
+  hipError_t e = batch_forces(b, mt, false, kind == 1 ? 1 : 0, nullptr);
   if (e == hipSuccess)
     e = kind == 0 ? launch_batch_combine_pre(mt, mp + o[6], o[7] - o[6], b->own)
                   : launch_batch_combine(mt, b->nmem, mp + o[6], o[7] - o[6], 0, b->own);
