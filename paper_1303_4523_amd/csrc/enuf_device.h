@@ -57,6 +57,27 @@ __device__ inline int mesh_cell(double x, double m_over_l, int M, double *t) {
   return c;
 }
 
+// 1/x and (sqrt(x), 1/sqrt(x)) of normal positive x from the hardware's
+// estimates (about 2^-24) by two Newton / Goldschmidt steps, to about an ulp.
+__device__ __forceinline__ double recip_f64(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(y, fma(-x, y, 1.0), y);
+  return fma(y, fma(-x, y, 1.0), y);
+}
+__device__ __forceinline__ void sqrt_rsqrt_f64(double x, double *root, double *inv) {
+#pragma clang fp contract(off)
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+  }
+  *root = fma(fma(-g, g, x), h, g);
+  *inv = h + h;
+}
+
 // Real-space cell of a wrapped position (x < L can still round to ncell).
 __device__ inline int cell_of(double x, double y, double z, const CellParams &cp) {
   int cx = (int)(x * cp.inv_cell), cy = (int)(y * cp.inv_cell), cz = (int)(z * cp.inv_cell);

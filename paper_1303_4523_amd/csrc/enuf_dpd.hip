@@ -255,9 +255,9 @@ constexpr int kPairZ = kPairSegMax + 2;  // staged z-slices at most
 constexpr int kPairCells = 9 * kPairZ;   // staged cells at most
 static_assert(kPairCells <= kPairThreads, "the prefix sum takes one staged cell per thread");
 static_assert(kPairCells <= 256, "staged cells are numbered in a byte");
-// candidate steps in flight per lane: 8 for one system (153 VGPRs, 3 waves
+// candidate steps in flight per lane: 8 for one system (145 VGPRs, 3 waves
 // per SIMD; 4.5 % less step time than 4 at N = 24000, where the kernel runs
-// beside the mesh passes); batches take 4 (122 VGPRs, 4 waves per SIMD; 8 %
+// beside the mesh passes); batches take 4 (118 VGPRs, 4 waves per SIMD; 8 %
 // less batch step time than 8, the batch filling the chip) or 8
 // (enuf_batch_set_tuning)
 constexpr int kPairU = 8;
@@ -287,13 +287,18 @@ __device__ __forceinline__ void
 dpd_pair_cells(const DpdParams &P, uint64_t step, gptr<const double4> __restrict__ cpos,
                gptr<const double4> __restrict__ cvel, PairShared &sh, const double4 *s_pos,
                const double4 *s_vel, const float4 *s_rel, int base, int zs, int ze, int nz, bool tiny) {
-  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  const int lane = threadIdx.x & (kWave - 1), w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int cap = P.cap;
   const double L = P.L, invL = 1.0 / L, isdt = 1.0 / sqrt(P.dt);
   int *qj = sh.qj[w], *qi = sh.qi[w];
   unsigned char *qa = sh.qa[w];
   const int own0 = sh.ownoff[zs];
 
+  // Bound by instruction issue: what is the same for the whole wavefront (its
+  // number, the own cell's bounds) is kept in scalar registers, the lane's
+  // particle and share come from a reciprocal instead of integer divisions, and
+  // 1/r from the hardware's estimate by two Newton steps (64 replicas of 3000
+  // to 48000 particles: 433 us a launch, 469 with divisions and vector bounds).
   auto wave_sync = []() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -323,7 +328,8 @@ dpd_pair_cells(const DpdParams &P, uint64_t step, gptr<const double4> __restrict
       double dx, dy, dz;
       const double r2 = dpd_sep(pi, pj, L, invL, dx, dy, dz);
       if (r2 < 1.0 && r2 != 0.0) {
-        const double r = sqrt(r2), ir = 1.0 / r;
+        double r, ir;
+        sqrt_rsqrt_f64(r2, &r, &ir);
         const double ex = dx * ir, ey = dy * ir, ez = dz * ir;
         const double wr = 1.0 - r;
         const double vdot = fma(vi.x - vj.x, ex, fma(vi.y - vj.y, ey, (vi.z - vj.z) * ez));
@@ -360,19 +366,22 @@ dpd_pair_cells(const DpdParams &P, uint64_t step, gptr<const double4> __restrict
   for (;;) {
     int zi = 0;
     if (lane == 0) zi = atomicAdd(&sh.next, 1);
-    zi = zs + __shfl(zi, 0, kWave);
+    zi = zs + __builtin_amdgcn_readfirstlane(zi);
     if (zi >= ze) break;
     const int ko = zi * 9 + 4;                  // the own column's cell of slice zi
-    const int a_lo = sh.off[ko], n_a = sh.off[ko + 1] - a_lo;
+    auto scalar = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    const int a_lo = scalar(sh.off[ko]), n_a = scalar(sh.off[ko + 1]) - a_lo;
     const int k0 = tiny ? 0 : (zi - 1) * 9, k1 = tiny ? nz * 9 : (zi + 2) * 9;
-    const int lo = sh.off[k0], T = sh.off[k1] - lo;
-    const int abase = sh.ownoff[zi] - own0;
+    const int lo = scalar(sh.off[k0]), T = scalar(sh.off[k1]) - lo;
+    const int abase = scalar(sh.ownoff[zi]) - own0;
     for (int a0 = 0; a0 < n_a; a0 += kWave) {
       const int g = (n_a - a0) < kWave ? (n_a - a0) : kWave;
-      const int m = kWave / g;
+      const float inv_g = 1.0f / (float)g;
+      int ar, rest;
+      int t = fdivmod(lane, g, inv_g, &ar);
+      const int m = __builtin_amdgcn_readfirstlane(fdivmod(kWave, g, inv_g, &rest));
       const bool act = lane < g * m;
-      const int a = a0 + lane % g;
-      int t = lane / g;
+      const int a = a0 + ar;
       const int ia = abase + a;
       const int iref = STAGED ? a_lo + a - base : sh.gcell[ko] * cap + a;
       float4 ri = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -411,7 +420,7 @@ dpd_pair_cells(const DpdParams &P, uint64_t step, gptr<const double4> __restrict
           }
           const unsigned long long bm = __ballot(take);
           if (take) {
-            const int at = qn + (int)__popcll(bm & __lanemask_lt());
+            const int at = qn + lanes_below(bm);
             qj[at] = jref[u];
             qi[at] = iref;
             qa[at] = (unsigned char)ia;
@@ -436,7 +445,7 @@ dpd_pair_body(const DpdParams &P, uint64_t step, gptr<const double> __restrict__
               gptr<const int> __restrict__ bond_to, gptr<double> __restrict__ fdpd, int pb, int nb) {
   extern __shared__ __align__(16) unsigned char pair_smem[];
   __shared__ PairShared sh;
-  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  const int lane = threadIdx.x & (kWave - 1), w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lb = (pb % kXcds) * (nb / kXcds) + pb / kXcds;  // XCD-contiguous logical block
   const int n = P.ncell, cap = P.cap;
   const int col = lb / P.nseg, seg = lb % P.nseg;
@@ -454,8 +463,8 @@ dpd_pair_body(const DpdParams &P, uint64_t step, gptr<const double> __restrict__
     const int ox = c9 / 3 - 1, oy = c9 % 3 - 1;
     int c = 0, cnt = 0;
     if (dpd_offset_valid(ox, n) && dpd_offset_valid(oy, n)) {
-      const int z = tiny ? zsl : mod_pos(z0 - 1 + zsl, n);
-      c = (mod_pos(cx + ox, n) * n + mod_pos(cy + oy, n)) * n + z;
+      const int z = tiny ? zsl : wrap_once(z0 - 1 + zsl, n);
+      c = (wrap_once(cx + ox, n) * n + wrap_once(cy + oy, n)) * n + z;
       cnt = dcnt[c];
       cnt = cnt < cap ? cnt : cap;
     }
@@ -479,10 +488,15 @@ dpd_pair_body(const DpdParams &P, uint64_t step, gptr<const double> __restrict__
     for (int q = 0; q < w; ++q) b += sh.wsum[q];
     if (k < ncells) sh.off[k] = b + x - v;
     if (k == ncells - 1) sh.off[ncells] = b + x;
-    if (k <= nz) {
-      int s = 0;
-      for (int z = 0; z < k; ++z) s += sh.cnt[z * 9 + 4];
-      sh.ownoff[k] = s;
+    if (w == 0) {  // (nz + 1 <= 64)
+      const int v4 = lane < nz ? sh.cnt[lane * 9 + 4] : 0;
+      int s = v4;
+#pragma unroll
+      for (int o = 1; o < 32; o <<= 1) {
+        const int y = __shfl_up(s, o, kWave);
+        if (lane >= o) s += y;
+      }
+      if (lane <= nz) sh.ownoff[lane] = s - v4;
     }
     __syncthreads();
   }
@@ -562,22 +576,30 @@ dpd_pair_body(const DpdParams &P, uint64_t step, gptr<const double> __restrict__
     }
     if (threadIdx.x == 0) sh.next = 0;
     __syncthreads();
+    // where each own particle's bonds start, read ahead of the scan (a thread per
+    // own particle)
+    int bi = 0, b0 = 0, b1 = 0;
+    double4 be = make_double4(0.0, 0.0, 0.0, 0.0);
+    if ((int)threadIdx.x < nown) {
+      int zi = zs;
+      while (sh.ownoff[zi + 1] - sh.ownoff[zs] <= (int)threadIdx.x) ++zi;
+      const int a = threadIdx.x - (sh.ownoff[zi] - sh.ownoff[zs]), ko = zi * 9 + 4;
+      be = staged ? s_pos[sh.off[ko] + a - base] : gload(cpos + (sh.gcell[ko] * cap + a));
+      bi = (int)be.w;
+      b0 = bond_start[bi];
+      b1 = bond_start[bi + 1];
+    }
     if (staged)
       dpd_pair_cells<U, true, VLDS>(P, step, cpos, cvel, sh, s_pos, s_vel, s_rel, base, zs, ze, nz, tiny);
     else
       dpd_pair_cells<U, false, VLDS>(P, step, cpos, cvel, sh, s_pos, s_vel, s_rel, base, zs, ze, nz, tiny);
     __syncthreads();
     // bonds, F_i = -K (r - r0) rhat_ij, and the force of each own particle
-    for (int t = threadIdx.x; t < nown; t += kPairThreads) {
-      int zi = zs;
-      while (sh.ownoff[zi + 1] - sh.ownoff[zs] <= t) ++zi;
-      const int a = t - (sh.ownoff[zi] - sh.ownoff[zs]);
-      const int ko = zi * 9 + 4;
-      const double4 e = staged ? s_pos[sh.off[ko] + a - base] : gload(cpos + (sh.gcell[ko] * cap + a));
-      const int i = (int)e.w;
+    if ((int)threadIdx.x < nown) {
+      const int t = threadIdx.x, i = bi;
+      const double4 e = be;
       long long fx = (long long)sh.acc[t][0], fy = (long long)sh.acc[t][1], fz = (long long)sh.acc[t][2];
-      const int b1 = bond_start[i + 1];
-      for (int b = bond_start[i]; b < b1; ++b) {
+      for (int b = b0; b < b1; ++b) {
         const int j = bond_to[b];
         const double4 pj = make_double4(pos[3 * j], pos[3 * j + 1], pos[3 * j + 2], 0.0);
         double dx, dy, dz;

@@ -191,27 +191,6 @@ k_prep_compact(int64_t N, const double *__restrict__ pos, const double *__restri
 // g1 = sum_{n>=1} 2^n z^{2n-2}/(2n+1)!! (z = a r; the erf series is
 // Abramowitz & Stegun 7.1.6).
 // ---------------------------------------------------------------------------
-// 1/x and (sqrt(x), 1/sqrt(x)) of normal positive x from the hardware's
-// estimates (about 2^-24) by two Newton / Goldschmidt steps, to about an ulp.
-__device__ __forceinline__ double recip_f64(double x) {
-  double y = __builtin_amdgcn_rcp(x);
-  y = fma(y, fma(-x, y, 1.0), y);
-  return fma(y, fma(-x, y, 1.0), y);
-}
-__device__ __forceinline__ void sqrt_rsqrt_f64(double x, double *root, double *inv) {
-#pragma clang fp contract(off)
-  const double y = __builtin_amdgcn_rsq(x);
-  double g = x * y, h = 0.5 * y;
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const double e = fma(-h, g, 0.5);
-    g = fma(g, e, g);
-    h = fma(h, e, h);
-  }
-  *root = fma(fma(-g, g, x), h, g);
-  *inv = h + h;
-}
-
 // Coefficient tables of the pair function, highest power first (fitted in 60
 // to 90 digits).
 //  * E(s) = erf(z)/z and G(s) = (erf(z)/z - (2/sqrt(pi)) e^{-s})/s, s = z^2:
