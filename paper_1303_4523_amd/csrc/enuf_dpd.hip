@@ -330,6 +330,7 @@ dpd_pair_cells(const DpdParams &P, uint64_t step, gptr<const double4> __restrict
       if (r2 < 1.0 && r2 != 0.0) {
         double r, ir;
         sqrt_rsqrt_f64(r2, &r, &ir);
+        ir = fma(fma(-r, ir, 1.0), ir, ir);  // rounded as 1.0 / r is
         const double ex = dx * ir, ey = dy * ir, ez = dz * ir;
         const double wr = 1.0 - r;
         const double vdot = fma(vi.x - vj.x, ex, fma(vi.y - vj.y, ey, (vi.z - vj.z) * ez));
