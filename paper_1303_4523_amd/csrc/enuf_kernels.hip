@@ -326,10 +326,10 @@ __device__ __forceinline__ RealParams real_params(double alpha, double rc2, doub
 }
 
 // The pair function at squared distance r2 <= r_cut^2: energies u (whole) and
-// us (Slater part), force factor f and the distance.  False for two point
-// charges at the same place.
+// us (Slater part), force factor f and 1/r.  False for two point charges at
+// the same place.
 __device__ __forceinline__ bool real_pair(const RealParams &p, double r2, double *u, double *us, double *f,
-                                          double *r_out) {
+                                          double *ir_out) {
   // no contraction left to the compiler: every instantiation of the
   // real-space kernels rounds these terms alike (a system's forces are
   // bitwise the same alone and in a batch)
@@ -340,7 +340,7 @@ __device__ __forceinline__ bool real_pair(const RealParams &p, double r2, double
   sqrt_rsqrt_f64(r2, &r, &ir);
   r = r2 > 0.0 ? r : 0.0;
   ir = r2 > 0.0 ? ir : 0.0;
-  *r_out = r;
+  *ir_out = ir;
   double e, g;  // alpha E, alpha^3 G
   double ee = 0.0, ff = 0.0;  // erfc form: erfc(a r)/r and its force factor
   if (p.groups > 0) {
@@ -464,6 +464,9 @@ struct RealShared {
   double shift[kRealCells][3];            // to the image next to the segment, relative to its first cell
   unsigned short list[kRealWaves][kRealU][kRealStage];  // candidates that passed, per charge of the unit
   unsigned char cellof[kRealStage];       // staged cell of each candidate
+  ushort2 redo[kRealThreads];             // pairs (candidate, charge) for real_redo, of the block
+  ushort2 spare[kRealWaves][kWave];       // and of a wavefront when there is no room
+  int nredo;
 };
 
 // A lane's running sum of terms rounded to multiples of 1 / kRealFxScale: v x
@@ -478,6 +481,13 @@ __device__ __forceinline__ void real_add(double &sum, double v) {
 #pragma clang fp contract(off)
   sum += (v * kRealFxScale + kRealMagic) - kRealMagic;
 }
+// The same term rounded, and how far the rounding moved it (at most 1/2).
+__device__ __forceinline__ double real_round(double v, double *moved) {
+#pragma clang fp contract(off)
+  const double t = v * kRealFxScale, k = (t + kRealMagic) - kRealMagic;
+  *moved = fabs(t - k);
+  return k;
+}
 __device__ __forceinline__ unsigned long long real_sum(double sum) {
   return (unsigned long long)(__double_as_longlong(sum + kRealMagic) - __double_as_longlong(kRealMagic));
 }
@@ -490,6 +500,69 @@ __device__ __forceinline__ float real_pretest_r2(double rc2, double L) {
   frexp(L, &e);  // L < 2^e
   const double rc = sqrt(rc2) + 8.0 * ldexp(1.0, e - 24);
   return (float)(rc * rc * (1.0 + 1.0e-6));
+}
+
+// The force factor of the pair function from the library's erfc and exp.
+__device__ __forceinline__ double real_factor(double r, double a, double lam) {
+#pragma clang fp contract(off)
+  const double k2 = 1.1283791670955125739;  // 2/sqrt(pi)
+  if (lam > 0.0 && r < 0.5 * lam) {
+    const double x = r / lam, y = 2.0 * x, z = a * r, z2 = z * z;
+    double b2 = 4.0 / 3.0, term = 4.0 / 3.0;
+#pragma unroll 1
+    for (int n = 4; n < 30; ++n) {
+      term *= y / n;
+      b2 += term;
+    }
+    double t1 = 2.0 / 3.0, g1 = 0.0;
+#pragma unroll 1
+    for (int n = 1; n < 20; ++n) {
+      g1 += t1;
+      t1 *= 2.0 * z2 / (2.0 * n + 3.0);
+    }
+    const double ex = exp(-y), ez = exp(-z2);
+    return (r > 0.0) ? (ex * b2 / (lam * lam * lam) - k2 * a * a * a * ez * g1) : 0.0;
+  }
+  const double ar = a * r, r2 = r * r;
+  double ff = (erfc(ar) / r + k2 * a * exp(-ar * ar)) / r2;
+  if (lam > 0.0) {
+    const double x = r / lam;
+    ff -= (1.0 + 2.0 * x + 2.0 * x * x) * exp(-2.0 * x) / (r2 * r);
+  }
+  return ff;
+}
+
+// The polynomials and the library agree to kRealSlack of |qq| / r^2.  A force
+// term whose rounding to fixed point that much could change (one pair in
+// several hundred), or that is too large for real_add, is left to real_redo,
+// which takes the library's value: the rounded terms, and so whole
+// trajectories, are those of the library's functions.  Measured: 60001 particles,
+// 70 % of them charged, divalent ions: 301 us an evaluation, 288 without the
+// second evaluation, 388 with the library's functions for all pairs; listing
+// the pairs in LDS and calling once a window keeps the call's registers out of
+// the loops (called in the loop: 411).
+constexpr double kRealSlack = 3.552713678800501e-15;  // 2^-48
+__device__ __attribute__((noinline)) int real_redo(RealShared *sh, const ushort2 *pairs, int n, double L, double alpha,
+                                                   double lam) {
+#pragma clang fp contract(off)
+  const double invL = 1.0 / L;
+  const int lane = threadIdx.x & (kWave - 1);
+  int err = 0;
+  if (lane < n) {
+    const ushort2 e = pairs[lane];
+    const double4 pi = sh->own[e.y], pj = sh->pos[e.x];
+    double dx = pi.x - pj.x, dy = pi.y - pj.y, dz = pi.z - pj.z;
+    dx = fma(-L, rint(dx * invL), dx);
+    dy = fma(-L, rint(dy * invL), dy);
+    dz = fma(-L, rint(dz * invL), dz);
+    const double r = sqrt(fma(dx, dx, fma(dy, dy, dz * dz)));
+    const double gf = pi.w * pj.w * real_factor(r, alpha, lam);
+    if (fabs(gf) * r * kRealFxScale > kFxLimit) err = kEOverflow;
+    atomicAdd(&sh->acc[e.y][0], (unsigned long long)to_fixed(gf * dx, kRealFxScale));
+    atomicAdd(&sh->acc[e.y][1], (unsigned long long)to_fixed(gf * dy, kRealFxScale));
+    atomicAdd(&sh->acc[e.y][2], (unsigned long long)to_fixed(gf * dz, kRealFxScale));
+  }
+  return err;
 }
 
 // The charges of segment [z0, z0 + zn) of column (cx, cy), those with place
@@ -541,7 +614,10 @@ real_segment(RealShared &sh, gptr<const int> __restrict__ ccnt, gptr<const doubl
       sh.shift[lane][1] = (Y < 0 ? -L : (Y >= n ? L : 0.0)) - cy * edge;
       sh.shift[lane][2] = (Z < 0 ? -L : (Z >= n ? L : 0.0)) - z0 * edge;
     }
-    if (lane == 0) sh.off[ncells] = total;
+    if (lane == 0) {
+      sh.off[ncells] = total;
+      sh.nredo = 0;
+    }
   }
   const double invL = 1.0 / L;
   const float rc2f = n < 3 ? 3.0e38f : real_pretest_r2(rc2, L);
@@ -652,6 +728,7 @@ real_segment(RealShared &sh, gptr<const int> __restrict__ ccnt, gptr<const doubl
           const int sub = lane / kRealLanes, ia = a + sub < hi - a0 ? a + sub : a;
           const double4 pi = sh.own[ia];
           double fx = 0.0, fy = 0.0, fz = 0.0, eu = 0.0, es = 0.0;
+          int again = 0;  // pairs of the lane's charge left to real_redo
           int nl[kRealU];
 #pragma unroll
           for (int v = 0; v < kRealU; ++v) nl[v] = 0;
@@ -681,42 +758,53 @@ real_segment(RealShared &sh, gptr<const int> __restrict__ ccnt, gptr<const doubl
               // minimum image and r^2 with their fused multiply-adds written
               // out (no contraction left to the compiler, as in real_pair)
 #pragma clang fp contract(off)
-              if (k >= mine) continue;
-              const int ij = sh.list[w][sub][k];
-              const double4 pj = sh.pos[ij];
-              double dx = pi.x - pj.x, dy = pi.y - pj.y, dz = pi.z - pj.z;
-              dx = fma(-L, rint(dx * invL), dx);
-              dy = fma(-L, rint(dy * invL), dy);
-              dz = fma(-L, rint(dz * invL), dz);
-              const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-              // the charge itself, or inside the FP32 margin only
-              if (ij * nwin + win == own0 + ia || !(r2 < rc2)) continue;
-              double u, us, f, r;
-              if (!real_pair(rp, r2, &u, &us, &f, &r)) {
-                err = kECoincident;
-                continue;
-              }
-              const double qq = pi.w * pj.w;
-              const double gf = qq * f;
-              const double big = fabs(gf) * r * kRealFxScale;
-              if (__builtin_expect(big < kRealSmall, 1)) {
-                real_add(fx, gf * dx);
-                real_add(fy, gf * dy);
-                real_add(fz, gf * dz);
-              } else {
-                if (big > kFxLimit) err = kEOverflow;
-                atomicAdd(&sh.acc[ia][0], (unsigned long long)to_fixed(gf * dx, kRealFxScale));
-                atomicAdd(&sh.acc[ia][1], (unsigned long long)to_fixed(gf * dy, kRealFxScale));
-                atomicAdd(&sh.acc[ia][2], (unsigned long long)to_fixed(gf * dz, kRealFxScale));
-              }
-              if (energies && __float_as_int(sh.rel[ij].w) > __float_as_int(sh.ownf[ia].w)) {
-                if (__builtin_expect(fmax(fabs(qq * u), fabs(qq * us)) * kRealFxScale < kRealSmall, 1)) {
-                  real_add(eu, qq * u);
-                  real_add(es, qq * us);
-                } else {
-                  atomicAdd(&sh.acc[ia][3], (unsigned long long)to_fixed(qq * u, kRealFxScale));
-                  atomicAdd(&sh.acc[ia][4], (unsigned long long)to_fixed(qq * us, kRealFxScale));
+              bool redo = false;
+              int ij = 0;
+              if (k < mine) {
+                ij = sh.list[w][sub][k];
+                const double4 pj = sh.pos[ij];
+                double dx = pi.x - pj.x, dy = pi.y - pj.y, dz = pi.z - pj.z;
+                dx = fma(-L, rint(dx * invL), dx);
+                dy = fma(-L, rint(dy * invL), dy);
+                dz = fma(-L, rint(dz * invL), dz);
+                const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
+                // (not the charge itself, nor inside the FP32 margin only)
+                if (ij * nwin + win != own0 + ia && r2 < rc2) {
+                  double u, us, f, ir;
+                  if (!real_pair(rp, r2, &u, &us, &f, &ir)) {
+                    err = kECoincident;
+                  } else {
+                    const double qq = pi.w * pj.w;
+                    const double gf = qq * f;
+                    double mx, my, mz;
+                    const double kx = real_round(gf * dx, &mx), ky = real_round(gf * dy, &my),
+                                 kz = real_round(gf * dz, &mz);
+                    const double slack = fabs(qq) * (kRealSlack * kRealFxScale) * (ir * ir * ir);
+                    redo = !(fma(slack, fabs(dx), mx) < 0.5 && fma(slack, fabs(dy), my) < 0.5 &&
+                             fma(slack, fabs(dz), mz) < 0.5 && fabs(gf) * kRealFxScale < kRealSmall * ir);
+                    if (!redo) {
+                      fx += kx;
+                      fy += ky;
+                      fz += kz;
+                    }
+                    if (energies && __float_as_int(sh.rel[ij].w) > __float_as_int(sh.ownf[ia].w)) {
+                      if (__builtin_expect(fmax(fabs(qq * u), fabs(qq * us)) * kRealFxScale < kRealSmall, 1)) {
+                        real_add(eu, qq * u);
+                        real_add(es, qq * us);
+                      } else {
+                        atomicAdd(&sh.acc[ia][3], (unsigned long long)to_fixed(qq * u, kRealFxScale));
+                        atomicAdd(&sh.acc[ia][4], (unsigned long long)to_fixed(qq * us, kRealFxScale));
+                      }
+                    }
+                  }
                 }
+              }
+              // (kept in the list's front: those places have been read)
+              const unsigned long long mk = __ballot(redo);
+              if (mk) {
+                const unsigned row = (unsigned)(mk >> (kRealLanes * sub)) & ((1u << kRealLanes) - 1u);
+                if (redo) sh.list[w][sub][again + __popc(row & ((1u << (lane % kRealLanes)) - 1u))] = (unsigned short)ij;
+                again += __popc(row);
               }
             }
           }
@@ -739,9 +827,46 @@ real_segment(RealShared &sh, gptr<const int> __restrict__ ccnt, gptr<const doubl
               atomicAdd(&sh.acc[ia][4], real_sum(es));
             }
           }
+          // pairs for real_redo to the block's list; beyond its end the
+          // wavefront takes them at once
+          if (__ballot(again > 0)) {
+            wave_sync();
+#pragma unroll 1
+            for (int v = 0; v < kRealU; ++v) {
+              const int nv = __builtin_amdgcn_readlane(again, kRealLanes * v);
+#pragma unroll 1
+              for (int b = 0; b < nv; b += kWave) {
+                const int m = nv - b < kWave ? nv - b : kWave;
+                int at = 0;
+                if (lane == 0) at = atomicAdd(&sh.nredo, m);
+                at = __builtin_amdgcn_readfirstlane(at);
+                // the first `fit` of them into the list
+                const int fit = at < kRealThreads ? (kRealThreads - at < m ? kRealThreads - at : m) : 0;
+                ushort2 *dst = lane < fit ? sh.redo + at + lane : sh.spare[w] + (lane - fit);
+                if (lane < m) *dst = make_ushort2(sh.list[w][v][b + lane], (unsigned short)(a + v));
+                wave_sync();
+                if (fit < m) {
+                  const int e = real_redo(&sh, sh.spare[w], m - fit, L, rp.a, rp.lam);
+                  err = e ? e : err;
+                  wave_sync();
+                }
+              }
+            }
+          }
         }
       }
       __syncthreads();
+      int nredo = __builtin_amdgcn_readfirstlane(sh.nredo);
+      if (nredo) {
+        nredo = nredo < kRealThreads ? nredo : kRealThreads;
+        if (w * kWave < nredo) {
+          const int m = nredo - w * kWave < kWave ? nredo - w * kWave : kWave;
+          const int e = real_redo(&sh, sh.redo + w * kWave, m, L, rp.a, rp.lam);
+          err = e ? e : err;
+        }
+        __syncthreads();
+        if (tid == 0) sh.nredo = 0;
+      }
     }
     for (int k = tid; k < nown * 5; k += kRealThreads) {
       const int a = k / 5, t = k % 5;

@@ -51,3 +51,24 @@ def test_real_space_routes(L, r_cut, n, alpha, lam):
     scale = sum(abs(ref[k]) for k in ("E_real", "E_recip", "E_self"))
     assert abs(E[0] - ref["E_real"]) <= 1e-8 * scale
     assert abs(E[1] - ref["E_slater"]) <= 1e-8 * scale
+
+
+@pytest.mark.parametrize("q0", [1.0, 30.0, 100.0])
+def test_real_space_terms_left_to_the_library(q0):
+    """Charges so large that few (1), many (30) or all (100) of a block's pairs
+    are left to the second evaluation, more than its list holds among them."""
+    import torch
+
+    from paper_1303_4523_amd import Plan
+    L, r_cut, alpha, lam, n = 5.9, 2.0, 0.45, 0.25, 402
+    rng = np.random.Generator(np.random.PCG64(7))
+    pos = rng.uniform(0.0, L, size=(n, 3))
+    q = q0 * np.where(np.arange(n) % 2 == 0, 1.0, -1.0)
+    ref = oracle.ewald(pos, q, L, alpha, 8, r_cut, lam)
+    plan = Plan(n, L, alpha, 8, 2.0, 32, 8, r_cut, lam, device=0)
+    F, E = plan.compute_components(torch.tensor(pos, device="cuda"), torch.tensor(q, device="cuda"))
+    F, E = F.cpu().numpy(), E.cpu().numpy()
+    assert plan.status() == 0
+    plan.close()
+    assert np.linalg.norm(F - ref["F"]) <= 1e-8 * np.linalg.norm(ref["F"])
+    assert abs(E[0] - ref["E_real"]) <= 1e-8 * sum(abs(ref[k]) for k in ("E_real", "E_recip", "E_self"))
