@@ -212,14 +212,10 @@ __device__ inline long long to_fixed_fast(double v, double scale) {
 // (j / Ns) Ns R + k + r Ns, which leaves the result in natural order after
 // the last pass.  Passes are done in place: each thread first loads all of
 // its butterflies into registers, the block synchronises, then stores.
-// Lines are processed in groups small enough for MaxBfly butterflies per
-// thread.  inverse: the unnormalised inverse via conj(FFT(conj(x))).
+// A sweep takes as many lines as there are threads, one butterfly each: a
+// radix-8 butterfly already holds 16 values.  inverse: the unnormalised inverse via conj(FFT(conj(x))).
 // All threads of the block must call this function.
 // ---------------------------------------------------------------------------
-// Butterflies per thread per sweep.  One: a radix-8 butterfly already holds
-// 16 values, and the mesh kernels run at the edge of their register budget.
-template <typename T, int R> struct MaxBfly { static constexpr int value = 1; };
-
 template <typename T, int R>
 __device__ __forceinline__ void dft_radix(T *xr, T *xi) {
   if constexpr (R == 2) {
@@ -287,57 +283,71 @@ __device__ __forceinline__ void dft_radix(T *xr, T *xi) {
 // (lpb lines per sweep): its index arithmetic and its R - 1 twiddles are the
 // same for every line, so they are computed once per pass, not per butterfly.
 template <typename T, int R>
-__device__ __forceinline__ void stockham_pass(T *re, T *im, int ls, int nlines, int n, int Ns, const T *twr,
+__device__ __forceinline__ void stockham_pass(T *re, T *im, int ls, int nlines, int n, int Ns, int tstep, const T *twr,
                               const T *twi, bool conj_in, bool conj_out) {
-  const int nt = blockDim.x, tid = threadIdx.x;
+  // the thread index is opaque to each pass: else every radix's index
+  // arithmetic is computed ahead and held in registers across all passes and
+  // transforms of a kernel (170-256 VGPRs, two waves per SIMD)
+  const int nt = blockDim.x;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
   const int nb = n / R;                 // butterflies per line (<= n / 2 < blockDim.x)
-  const int tstep = n / (Ns * R);
-  const int lpb = nt / nb;              // lines per sweep step
-  const int lrow = tid / nb, j = tid - lrow * nb;
-  const bool active = lrow < lpb;
-  const int k = j % Ns;
-  const int ob = (j / Ns) * Ns * R + k;  // output offset of the butterfly within its line
-  T wr[R], wi[R];
-#pragma unroll
-  for (int r = 1; r < R; ++r) {
-    const int ti = k * r * tstep;
-    wr[r] = twr[ti];
-    wi[r] = twi[ti];
+  int lpb, lrow, j, q, k;               // lines per sweep step; this thread's line, butterfly, j div Ns, j mod Ns
+  if (__builtin_constant_p(nb)) {
+    lpb = nt / nb;
+    lrow = tid / nb;
+    j = tid - lrow * nb;
+    q = j / Ns;
+    k = j - q * Ns;
+  } else {
+    // four integer divisions by run-time values were a third of a pass
+    const float inv_nb = __builtin_amdgcn_rcpf((float)nb);
+    int rem;
+    lpb = __builtin_amdgcn_readfirstlane(fdivmod(nt, nb, inv_nb, &rem));
+    lrow = fdivmod(tid, nb, inv_nb, &j);
+    q = fdivmod(j, Ns, __builtin_amdgcn_rcpf((float)Ns), &k);
   }
-  constexpr int kMaxBfly = MaxBfly<T, R>::value;
-  for (int l0 = 0; l0 < nlines; l0 += lpb * kMaxBfly) {
-    T vr[kMaxBfly][R], vi[kMaxBfly][R];
+  const bool active = lrow < lpb;
+  const int ob = q * Ns * R + k;        // output offset of the butterfly within its line
+  const bool turn = Ns > 1;             // the first pass has no twiddles
+  T wr[R], wi[R];
+  if (turn) {
 #pragma unroll
-    for (int q = 0; q < kMaxBfly; ++q) {
-      const int line = l0 + lrow + q * lpb;
-      if (active && line < nlines) {
-        const int base = line * ls + j;
+    for (int r = 1; r < R; ++r) {
+      const int ti = k * r * tstep;
+      wr[r] = twr[ti];
+      wi[r] = twi[ti];
+    }
+  }
+  for (int l0 = 0; l0 < nlines; l0 += lpb) {
+    T vr[R], vi[R];
+    const int line = l0 + lrow;
+    const bool on = active && line < nlines;
+    if (on) {
+      const int base = line * ls + j;
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          vr[q][r] = re[base + r * nb];
-          const T v = im[base + r * nb];
-          vi[q][r] = conj_in ? -v : v;
-        }
+      for (int r = 0; r < R; ++r) {
+        vr[r] = re[base + r * nb];
+        const T v = im[base + r * nb];
+        vi[r] = conj_in ? -v : v;
       }
     }
     __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kMaxBfly; ++q) {
-      const int line = l0 + lrow + q * lpb;
-      if (active && line < nlines) {
+    if (on) {
+      if (turn) {
 #pragma unroll
         for (int r = 1; r < R; ++r) {
-          const T xr = vr[q][r], xi = vi[q][r];
-          vr[q][r] = xr * wr[r] - xi * wi[r];
-          vi[q][r] = xr * wi[r] + xi * wr[r];
+          const T xr = vr[r], xi = vi[r];
+          vr[r] = xr * wr[r] - xi * wi[r];
+          vi[r] = xr * wi[r] + xi * wr[r];
         }
-        dft_radix<T, R>(vr[q], vi[q]);
-        const int o = line * ls + ob;
+      }
+      dft_radix<T, R>(vr, vi);
+      const int o = line * ls + ob;
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          re[o + r * Ns] = vr[q][r];
-          im[o + r * Ns] = conj_out ? -vi[q][r] : vi[q][r];
-        }
+      for (int r = 0; r < R; ++r) {
+        re[o + r * Ns] = vr[r];
+        im[o + r * Ns] = conj_out ? -vi[r] : vi[r];
       }
     }
     __syncthreads();
@@ -349,7 +359,7 @@ __device__ __forceinline__ void stockham_pass(T *re, T *im, int ls, int nlines, 
 template <typename T, bool INV, int N, int NS, int R, int... Rest>
 __device__ __forceinline__ void fft_passes(T *re, T *im, int ls, int nlines, const T *twr, const T *twi) {
   constexpr bool first = NS == 1, last = sizeof...(Rest) == 0;
-  stockham_pass<T, R>(re, im, ls, nlines, N, NS, twr, twi, INV && first, INV && last);
+  stockham_pass<T, R>(re, im, ls, nlines, N, NS, N / (NS * R), twr, twi, INV && first, INV && last);
   if constexpr (!last) fft_passes<T, INV, N, NS * R, Rest...>(re, im, ls, nlines, twr, twi);
 }
 
@@ -372,16 +382,18 @@ __device__ __forceinline__ void lds_fft(T *re, T *im, int ls, int nlines, const 
     case 128: fft_fixed<T, 128, 8, 4, 4>(re, im, ls, nlines, twr, twi, inverse); return;
     default: break;
   }
-  int Ns = 1;
+  int Ns = 1, left = pl.n;  // left: n / Ns
   for (int ps = 0; ps < pl.npass; ++ps) {
     const int R = pl.radix[ps];
+    int n = pl.n;  // opaque to each pass, as the thread index is (stockham_pass)
+    asm volatile("" : "+s"(n));
     const bool ci = inverse && ps == 0, co = inverse && ps == pl.npass - 1;
     switch (R) {
-      case 2: stockham_pass<T, 2>(re, im, ls, nlines, pl.n, Ns, twr, twi, ci, co); break;
-      case 3: stockham_pass<T, 3>(re, im, ls, nlines, pl.n, Ns, twr, twi, ci, co); break;
-      case 4: stockham_pass<T, 4>(re, im, ls, nlines, pl.n, Ns, twr, twi, ci, co); break;
-      case 8: stockham_pass<T, 8>(re, im, ls, nlines, pl.n, Ns, twr, twi, ci, co); break;
-      default: stockham_pass<T, 5>(re, im, ls, nlines, pl.n, Ns, twr, twi, ci, co); break;
+      case 2: left /= 2, stockham_pass<T, 2>(re, im, ls, nlines, n, Ns, left, twr, twi, ci, co); break;
+      case 3: left /= 3, stockham_pass<T, 3>(re, im, ls, nlines, n, Ns, left, twr, twi, ci, co); break;
+      case 4: left /= 4, stockham_pass<T, 4>(re, im, ls, nlines, n, Ns, left, twr, twi, ci, co); break;
+      case 8: left /= 8, stockham_pass<T, 8>(re, im, ls, nlines, n, Ns, left, twr, twi, ci, co); break;
+      default: left /= 5, stockham_pass<T, 5>(re, im, ls, nlines, n, Ns, left, twr, twi, ci, co); break;
     }
     Ns *= R;
   }

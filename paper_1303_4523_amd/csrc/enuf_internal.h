@@ -121,7 +121,7 @@ struct MeshParams {
   int cheb_deg;    // degree of the value series (derivative: cheb_deg - 1)
   int xcap;        // slots per x-cell sub-bin of the charge binning
   int M;           // mesh points per side
-  int Mp;          // padded row stride of LDS planes (elements)
+  int Mp;          // padded row stride of LDS planes (elements): mesh_stride
   int Mz;          // padded line stride of LDS spectrum buffers (elements)
   int Kc;          // reciprocal cutoff: 0 < |k| < Kc
   int nky;         // 2 Kc - 1 stored ky values (ky = idx - (Kc - 1))
@@ -143,6 +143,19 @@ struct MeshParams {
   WindowParams win;
   FftPlan fft;
 };
+
+// Row stride of the LDS planes, odd (no bank conflicts between rows).  The
+// stencils of half-width 4 run up to 7 columns past the mesh instead of
+// wrapping along z.
+inline int mesh_stride(int M, int p) { return p == 4 ? M + 7 : M + 1; }
+
+// Whether the kernels of half-width 4 run (the LDS budget admits their rows).
+inline bool mesh_win8(const MeshParams &m) { return m.win.p == 4 && m.Mp == mesh_stride(m.M, 4); }
+
+// Entries of the window tables: value and derivative series [2][2p][D + 1]
+// and, for half-width 4, the rows read by window8 (16 wide; FP64 D/2 + 1 of
+// them, FP32 D + 1).
+inline size_t window_entries(int p, int D) { return 4 * (size_t)p * (D + 1) + (p == 4 ? 16 * (size_t)(D + 2) : 0); }
 
 // Byte offset of the field spectrum h within the gzy buffer (after the
 // fixed-point partial spectra of the plane parts).
@@ -198,7 +211,7 @@ struct ComputeBuffers {
   double4 *part;         // [N * 2p * nslot] gather partials (dwx A, wx By, wx Bz, wx A)
   int *xcnt;             // [2 M kXSub] charges per mesh x-cell sub-bin (zero between calls; two sets like ccnt)
   int *xslot;            // [M kXSub xcap] compact indices of the charges of each x-cell sub-bin
-  double *wcoef64;       // [2p (D+1) + 2p D] window series coefficients (value, then derivative)
+  double *wcoef64;       // [window_entries] window series coefficients
   float *wcoef32;
   double *blk_eg;        // [nblk] per-block sums of q * A
   // tables
@@ -298,7 +311,7 @@ int plan_tables(const ComputeConfig &c, int precision, PlanTables *t);
 // m.rows.
 void mesh_lds_bytes(const MeshParams &m, int precision, size_t *fwd, size_t *x, size_t *bwd);
 
-// Choose m.rows / m.nchunk / m.nslot: the fewest row chunks whose passes fit
+// Choose m.Mp and m.rows / m.nchunk / m.nslot: the fewest row chunks whose passes fit
 // in max_lds bytes.  Returns false when no chunking fits.
 bool mesh_choose_rows(MeshParams &m, int precision, size_t max_lds);
 

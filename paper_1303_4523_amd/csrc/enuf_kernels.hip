@@ -987,6 +987,15 @@ __device__ inline int plane_charge(int e, int P2, const int *pre, const int *cel
   return xslot[(size_t)cell[lo] * xcap + (e - pre[lo])];
 }
 
+// Place in the stage of each calling lane with take set: one LDS atomic per
+// wavefront (an atomic per lane on the one counter is served lane by lane).
+__device__ __forceinline__ int stage_slot(bool take, int *s_n) {
+  const unsigned long long m = __ballot(take);
+  int base = 0;
+  if (m && lanes_below(__ballot(true)) == 0) base = atomicAdd(s_n, (int)__popcll(m));  // the first active lane
+  return __builtin_amdgcn_readfirstlane(base) + lanes_below(m);
+}
+
 // Stage in LDS those of the plane's charges e0 .. e0 + cnt - 1 that belong to
 // this work-group's share of the plane (compact index j with j mod parts ==
 // part): position and charge, compact index and x-bin.  Returns how many.
@@ -1004,8 +1013,9 @@ __device__ inline int stage_plane_charges(int e0, int cnt, int P2, const int *pr
   for (int e = threadIdx.x; e < cnt; e += blockDim.x) {
     int b;
     const int j = plane_charge(e0 + e, P2, pre, cell, xslot, xcap, &b);
-    if (j % parts == part) {
-      const int k = atomicAdd(s_n, 1);
+    const bool take = j % parts == part;
+    const int k = stage_slot(take, s_n);
+    if (take) {
       s_c[k] = gload(xq + j);
       s_jb[2 * k] = j;
       s_jb[2 * k + 1] = b;
@@ -1027,8 +1037,8 @@ __device__ inline int plane_charge_slot(int total, int P2, const int *pre, const
 }
 __device__ inline int stage_plane_commit(bool take, int j, int b, const double4 &c, double4 *s_c, int *s_jb,
                                          int *s_n) {
+  const int k = stage_slot(take, s_n);
   if (take) {
-    const int k = atomicAdd(s_n, 1);
     s_c[k] = c;
     s_jb[2 * k] = j;
     s_jb[2 * k + 1] = b;
@@ -1045,6 +1055,193 @@ __device__ inline int cell_frac(double x, double m_over_l, int M, double *frac) 
   return c;
 }
 
+// The same with the product's rounding stated: rounded with the difference
+// (FUSED), or before it.  The mesh passes of half-width 4 round each fraction as
+// the general ones are compiled to (all fused in the spread, y before it in the
+// gather), so that both find the same windows to the last bit.
+template <bool FUSED>
+__device__ __forceinline__ int cell_frac_as(double x, double m_over_l, int M, double *frac) {
+#pragma clang fp contract(off)
+  double t;
+  const int c = mesh_cell(x, m_over_l, M, &t);
+  *frac = FUSED ? fma(x, m_over_l, -(double)c) : t - (double)c;
+  return c;
+}
+
+// ---------------------------------------------------------------------------
+// Windows of half-width 4 (the default): a lane takes a charge (or two of its
+// stencil rows) and evaluates the window at all 8 offsets of an axis itself.
+// The series are the same for every lane, so their coefficients come through
+// scalar registers, and no lane waits for another's values: the general path's
+// group of 8 lanes per charge reads 4 series per lane from LDS and exchanges 16
+// or 32 values, which kept the LDS busy for the whole loop (5,800 cycles per
+// 512 (charge, row) items of the gather against about 1,000 here).
+// FP64: offsets s and 7 - s mirror each other, so the window (and its
+//   derivative) at both is E(x^2) +- x O(x^2), x = 2 frac - 1; table rows k =
+//   highest power first, [E_0..3, O_0..3 of the values, then of the derivatives].
+// FP32: the Chebyshev series by Clenshaw's recurrence, as in clenshaw_n;
+//   table rows k = 0 .. D of [value series 0..7, derivative series 0..7].
+// ---------------------------------------------------------------------------
+template <typename T>
+using ctab = const __attribute__((address_space(4))) T *;
+
+__device__ __forceinline__ float fma_sc(float a, float b, float c) {
+  float d;
+  asm("v_fma_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+  return d;
+}
+
+// NA axes at once; w[a][s] the values, d[a][s] the derivatives (DER).
+template <int NA, bool DER>
+__device__ __forceinline__ void window8(ctab<double> tab, int D, const double (&x)[NA], double (&w)[NA][8],
+                                        double (&d)[NA][8]) {
+  constexpr int NC = DER ? 16 : 8;
+  double y[NA], v[NA][NC];
+#pragma unroll
+  for (int a = 0; a < NA; ++a) {
+    y[a] = x[a] * x[a];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) v[a][i] = 0.0;
+  }
+  double c[NC];  // a row ahead of its use
+#pragma unroll
+  for (int i = 0; i < NC; ++i) c[i] = tab[i];
+  for (int k = D / 2; k >= 0; --k) {
+    double next[NC];
+    tab += 16;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) next[i] = tab[i];  // (the table ends with a spare row)
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+#pragma unroll
+      for (int a = 0; a < NA; ++a) v[a][i] = fma_sc(v[a][i], y[a], c[i]);
+#pragma unroll
+    for (int i = 0; i < NC; ++i) c[i] = next[i];
+  }
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      w[a][i] = fma(x[a], v[a][4 + i], v[a][i]);
+      w[a][7 - i] = fma(-x[a], v[a][4 + i], v[a][i]);
+      if (DER) {
+        d[a][i] = fma(x[a], v[a][12 % NC + i], v[a][8 % NC + i]);
+        d[a][7 - i] = fma(x[a], v[a][12 % NC + i], -v[a][8 % NC + i]);
+      }
+    }
+}
+template <int NA, bool DER>
+__device__ __forceinline__ void window8(ctab<float> tab, int D, const float (&x)[NA], float (&w)[NA][8],
+                                        float (&d)[NA][8]) {
+  constexpr int NC = DER ? 16 : 8;
+  float x2[NA], b1[NA][NC], b2[NA][NC];
+#pragma unroll
+  for (int a = 0; a < NA; ++a) {
+    x2[a] = x[a] + x[a];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) b1[a][i] = b2[a][i] = 0.0f;
+  }
+  ctab<float> row = tab + 16 * D;
+  float c[NC];  // a row ahead of its use
+#pragma unroll
+  for (int i = 0; i < NC; ++i) c[i] = row[i];
+  for (int k = D; k >= 1; --k) {
+    float next[NC];
+    row -= 16;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) next[i] = row[i];
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+#pragma unroll
+      for (int a = 0; a < NA; ++a) {
+        const float t = fma_sc(x2[a], b1[a][i], c[i]) - b2[a][i];
+        b2[a][i] = b1[a][i];
+        b1[a][i] = t;
+      }
+#pragma unroll
+    for (int i = 0; i < NC; ++i) c[i] = next[i];
+  }
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+      const float t = fma_sc(x[a], b1[a][i], c[i]) - b2[a][i];
+      if (i < 8)
+        w[a][i] = t;
+      else
+        d[a][i % 8] = t;
+    }
+  }
+}
+
+// Bring the table's rows (64-byte lines) into the scalar cache ahead of their
+// use, so that they do not miss one after the other in the window loop: issued
+// at the start of a kernel, awaited (done) after its first barrier.
+template <typename T>
+struct TouchRows {
+  static constexpr int kLines = 14;
+  T v[kLines];
+  __device__ __forceinline__ TouchRows(ctab<T> tab, int rows) {
+    constexpr int kLine = 64 / (int)sizeof(T);
+#pragma unroll
+    for (int k = 0; k < kLines; ++k) v[k] = tab[k * kLine < rows * 16 ? k * kLine : 0];
+  }
+  __device__ __forceinline__ void done() const {
+#pragma unroll
+    for (int k = 0; k < kLines; ++k) asm volatile("" ::"s"(v[k]));
+  }
+};
+
+// Entry r of an 8-entry register array for a lane whose rows are sub, sub + L, ..
+template <int L, typename T>
+__device__ __forceinline__ T pick8(const T (&v)[8], int i, int sub) {
+  // the entries are read before the selects: a select of the addresses would
+  // put the array into scratch memory
+  T e[L];
+#pragma unroll
+  for (int t = 0; t < L; ++t) e[t] = v[i * L + t];
+  T r = e[0];
+#pragma unroll
+  for (int t = 1; t < L; ++t) r = sub == t ? e[t] : r;
+  return r;
+}
+
+// Spread of the staged charges [0, cnt), L lanes per charge (stencil rows sub,
+// sub + L, ...).  The accumulator rows have 7 more columns than the mesh, so
+// that a stencil never wraps along z (folded back after the spread).
+template <typename T, int L>
+__device__ __forceinline__ void spread8(const MeshParams &mp, ctab<T> tab, const T *cv, int Ds, const double4 *s_c,
+                                        const int *s_jb, int cnt, int r0, int nr, double scale, long long *acc) {
+  const int M = mp.M, D = mp.cheb_deg, sub = threadIdx.x % L;
+  for (int e = threadIdx.x / L; e < cnt; e += blockDim.x / L) {
+    const double4 c = s_c[e];
+    double fx, fy, fz;
+    cell_frac_as<true>(c.x, mp.m_over_l, M, &fx);
+    const int cy = cell_frac_as<true>(c.y, mp.m_over_l, M, &fy);
+    const int cz = cell_frac_as<true>(c.z, mp.m_over_l, M, &fz);
+    const T x[2] = {(T)(2.0 * fz - 1.0), (T)(2.0 * fy - 1.0)}, ux[1] = {(T)(2.0 * fx - 1.0)};
+    T w[2][8], none[2][8], wx[1];
+    window8<2, false>(tab, D, x, w, none);
+    const T *const ser[1] = {cv + (7 - s_jb[2 * e + 1]) * Ds};
+    clenshaw_n<T, 1>(ser, ux, D, wx);
+    const T qx = (T)c.w * wx[0];
+    const int bz = cz - 3, col = bz < 0 ? bz + M : bz;
+#pragma unroll
+    for (int i = 0; i < 8 / L; ++i) {
+      const int row = wrap_once(cy - 3 + i * L + sub, M) - r0;
+      const T wrow = qx * pick8<L>(w[1], i, sub);
+      if ((unsigned)row < (unsigned)nr) {
+        unsigned long long *a = reinterpret_cast<unsigned long long *>(acc) + row * mp.Mp + col;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const double v = (double)(wrow * w[0][u]);
+          atomicAdd(a + u, (unsigned long long)to_fixed(v, scale));
+        }
+      }
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Mesh pass 1: spread + z R2C FFT + y FFT for one x-plane.
 // The plane is processed in chunks of mp.rows mesh rows (all of it when it
@@ -1055,14 +1252,14 @@ __device__ inline int cell_frac(double x, double m_over_l, int M, double *frac) 
 // ---------------------------------------------------------------------------
 __device__ inline size_t align16(size_t v) { return (v + 15) & ~(size_t)15; }
 
-template <typename T>
+template <typename T, int P>
 __device__ __forceinline__ void
 recip_fwd_body(gptr<const double4> __restrict__ xq, gptr<const int> __restrict__ xcnt,
                gptr<const int> __restrict__ xslot, gptr<const T> __restrict__ wcoef,
                gptr<const DevScalars> __restrict__ sc, const MeshParams &mp,
                gptr<const typename CplxOf<T>::type> __restrict__ tw, gptr<longlong2> gfx, int x0, int part) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int M = mp.M, Mp = mp.Mp, Mz = mp.Mz, Kc = mp.Kc, p = mp.win.p, P2 = 2 * p, D = mp.cheb_deg;
+  const int M = mp.M, Mp = mp.Mp, Mz = mp.Mz, Kc = mp.Kc, p = P > 0 ? P : mp.win.p, P2 = 2 * p, D = mp.cheb_deg;
   const int R = mp.rows;
   const int P2pad = pow2_at_least(P2), lg_pad = __builtin_ctz(P2pad);
   const int tid = threadIdx.x, nt = blockDim.x, lane = tid & (kWave - 1);
@@ -1095,7 +1292,10 @@ recip_fwd_body(gptr<const double4> __restrict__ xq, gptr<const int> __restrict__
   }
   for (int k = tid; k < P2 * (D + 1); k += nt) cv[(k / (D + 1)) * Ds + k % (D + 1)] = wcoef[k];
   const double scale = sc->scale, inv_scale = sc->inv_scale;
+  const ctab<T> tab = (ctab<T>)(wcoef + 2 * P2 * (D + 1));  // (half-width 4)
+  const TouchRows<T> touch(tab, P == 4 ? (sizeof(T) == 8 ? D / 2 + 1 : D + 1) : 0);
   const int total = plane_bins(x0, M, p, xcnt, mp.xcap, pre, bcell);  // synchronises
+  if constexpr (P == 4) touch.done();
 
   const int gbase = lane & ~(P2pad - 1);
   for (int r0 = 0; r0 < M; r0 += R) {
@@ -1105,6 +1305,15 @@ recip_fwd_body(gptr<const double4> __restrict__ xq, gptr<const int> __restrict__
     for (int e0 = 0; e0 < total; e0 += mp.stage) {
     const int cnt = stage_plane_charges(e0, (total - e0) < mp.stage ? (total - e0) : mp.stage, P2, pre, bcell,
                                         xslot, mp.xcap, xq, part, mp.parts, s_c, s_jb, s_n);
+    if constexpr (P == 4) {
+      // few charges: more lanes per charge, as long as one round takes them all
+      if (4 * cnt <= nt)
+        spread8<T, 4>(mp, tab, cv, Ds, s_c, s_jb, cnt, r0, nr, scale, acc);
+      else if (2 * cnt <= nt)
+        spread8<T, 2>(mp, tab, cv, Ds, s_c, s_jb, cnt, r0, nr, scale, acc);
+      else
+        spread8<T, 1>(mp, tab, cv, Ds, s_c, s_jb, cnt, r0, nr, scale, acc);
+    } else {
     // whole wavefronts iterate together so that the group shuffles see every lane
     const int items = ((cnt * P2pad + kWave - 1) / kWave) * kWave;
     for (int it = tid; it < items; it += nt) {
@@ -1155,7 +1364,15 @@ recip_fwd_body(gptr<const double4> __restrict__ xq, gptr<const int> __restrict__
         }
       }
     }
+    }
     __syncthreads();  // before the next batch is staged, and before the conversion
+    }
+    if constexpr (P == 4) {  // the columns past the mesh belong to its first seven
+      for (int k = tid; k < nr * 7; k += nt) {
+        long long *row = acc + (size_t)(k / 7) * Mp;
+        row[k % 7] += row[M + k % 7];
+      }
+      __syncthreads();
     }
 
     // fixed point -> T rows (in place; FP32 rows move down in groups)
@@ -1216,12 +1433,12 @@ recip_fwd_body(gptr<const double4> __restrict__ xq, gptr<const int> __restrict__
   }
 }
 
-template <typename T>
+template <typename T, int P>
 __global__ void __launch_bounds__(kPassThreads)
 k_recip_fwd(const double4 *__restrict__ xq, const int *__restrict__ xcnt, const int *__restrict__ xslot,
             const T *__restrict__ wcoef, const DevScalars *__restrict__ sc, MeshParams mp,
             const typename CplxOf<T>::type *__restrict__ tw, longlong2 *gfx) {
-  recip_fwd_body<T>(to_g(xq), to_g(xcnt), to_g(xslot), to_g(wcoef), to_g(sc), mp, to_g(tw), to_g(gfx),
+  recip_fwd_body<T, P>(to_g(xq), to_g(xcnt), to_g(xslot), to_g(wcoef), to_g(sc), mp, to_g(tw), to_g(gfx),
                     blockIdx.x % mp.M, blockIdx.x / mp.M);
 }
 
@@ -1343,12 +1560,112 @@ k_recip_x(MeshParams mp, const double *__restrict__ atab,
   recip_x_body<T>(mp, to_g(atab), to_g(tw), to_g(sc), to_g(gfx), to_g(gzy), to_g(gzx), to_g(epart), blockIdx.x);
 }
 
+// Gather of the staged charges [0, cnt) from the plane, L lanes per charge as
+// in spread8 (the plane rows repeat their first 7 columns past the mesh).  The
+// rows are added in the order of the general path's lane butterfly.
+template <typename T, bool IK, int L>
+__device__ __forceinline__ void gather8(const MeshParams &mp, ctab<T> tab, const T *cv, const T *cd, int Ds,
+                                        const double4 *s_c, const int *s_jb, int cnt, int r0, int nr, int chunk,
+                                        int comp, const T *plane, gptr<double4> part) {
+  const int M = mp.M, D = mp.cheb_deg, R = mp.rows, nslot = mp.nslot, sub = threadIdx.x % L;
+  for (int e = threadIdx.x / L; e < cnt; e += blockDim.x / L) {
+    // rounding written out: a row's sum runs through fused multiply-adds, the
+    // rows are scaled, then added
+#pragma clang fp contract(off)
+    const double4 c = s_c[e];
+    const int j = s_jb[2 * e], sx = 7 - s_jb[2 * e + 1];
+    double fx, fy, fz;
+    cell_frac_as<true>(c.x, mp.m_over_l, M, &fx);
+    const int cy = cell_frac_as<false>(c.y, mp.m_over_l, M, &fy);
+    const int cz = cell_frac_as<true>(c.z, mp.m_over_l, M, &fz);
+    const T x[2] = {(T)(2.0 * fz - 1.0), (T)(2.0 * fy - 1.0)}, ux = (T)(2.0 * fx - 1.0);
+    T w[2][8], d[2][8], wx, dwx = (T)0;
+    window8<2, !IK>(tab, D, x, w, d);
+    if (IK) {
+      const T *const ser[1] = {cv + sx * Ds};
+      const T arg[1] = {ux};
+      T o[1];
+      clenshaw_n<T, 1>(ser, arg, D, o);
+      wx = o[0];
+    } else {
+      const T *const ser[2] = {cv + sx * Ds, cd + sx * Ds};
+      const T arg[2] = {ux, ux};
+      T o[2];
+      clenshaw_n<T, 2>(ser, arg, D, o);
+      wx = o[0];
+      dwx = o[1];
+    }
+    const int bz = cz - 3, col = bz < 0 ? bz + M : bz;
+    T A[8 / L], By[8 / L], Bz[8 / L];
+#pragma unroll
+    for (int i = 0; i < 8 / L; ++i) {
+      const int row = wrap_once(cy - 3 + i * L + sub, M) - r0;
+      T a = (T)0, b = (T)0;
+      if ((unsigned)row < (unsigned)nr) {
+        const T *h = plane + row * mp.Mp + col;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          a = fma(h[u], w[0][u], a);
+          if (!IK) b = fma(h[u], d[0][u], b);
+        }
+      }
+      const T wy = pick8<L>(w[1], i, sub), dy = IK ? (T)0 : pick8<L>(d[1], i, sub);
+      A[i] = wy * a;
+      By[i] = dy * a;
+      Bz[i] = wy * b;
+    }
+    auto rows = [&](T *v) {
+#pragma clang fp contract(off)
+#pragma unroll
+      for (int h = 4 / L; h >= 1; h /= 2)
+#pragma unroll
+        for (int i = 0; i < h; ++i) v[i] += v[i + h];
+      T r = v[0];
+#pragma unroll
+      for (int o = L / 2; o >= 1; o /= 2) r += __shfl_xor(r, o, kWave);
+      return r;
+    };
+    const T sA = rows(A), sBy = IK ? (T)0 : rows(By), sBz = IK ? (T)0 : rows(Bz);
+    if (sub == 0) {
+      // the chunk of the charge's first stencil row writes slot 0 (and clears
+      // slot 1 when all its rows are in that chunk); the chunk of its last row
+      // writes slot 1
+      int slot = 0;
+      bool write = true, clear1 = false;
+      if (nslot > 1) {
+        const int first = wrap_once(cy - 3, M) / R, last = wrap_once(cy + 4, M) / R;
+        write = chunk == first || chunk == last;
+        slot = chunk == first ? 0 : 1;
+        clear1 = chunk == first && first == last;
+      }
+      if (write) {
+        const gptr<double4> dst = part + ((size_t)j * 8 + sx) * nslot;
+        if (!IK) {
+          gstore(dst + slot, make_double4((double)(dwx * sA), (double)(wx * sBy), (double)(wx * sBz),
+                                          (double)(wx * sA)));
+          if (clear1) gstore(dst + 1, make_double4(0.0, 0.0, 0.0, 0.0));
+        } else {
+          // component comp of the field; the potential entry stays zero
+          const gptr<double> f = (gptr<double>)(dst + slot);
+          f[comp] = (double)(wx * sA);
+          if (comp == 0) f[3] = 0.0;
+          if (clear1) {
+            const gptr<double> f1 = (gptr<double>)(dst + 1);
+            f1[comp] = 0.0;
+            if (comp == 0) f1[3] = 0.0;
+          }
+        }
+      }
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Mesh pass 3: inverse y FFT, complex-to-real z FFT and gather for one plane.
 // Each lane of a work-item group sums its mesh row against the z window and
 // its derivative (shared across the group); the group reduces with shuffles.
 // ---------------------------------------------------------------------------
-template <typename T, bool IK>
+template <typename T, bool IK, int P>
 __device__ __forceinline__ void
 recip_bwd_body(gptr<const double4> __restrict__ xq, gptr<const int> __restrict__ xcnt,
                gptr<const int> __restrict__ xslot, gptr<const T> __restrict__ wcoef,
@@ -1357,7 +1674,7 @@ recip_bwd_body(gptr<const double4> __restrict__ xq, gptr<const int> __restrict__
                gptr<const typename CplxOf<T>::type> __restrict__ gzy,
                gptr<const typename CplxOf<T>::type> __restrict__ gzx, gptr<double4> part, int x0, int wpart) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int M = mp.M, Mp = mp.Mp, Mz = mp.Mz, Kc = mp.Kc, nky = mp.nky, p = mp.win.p, P2 = 2 * p;
+  const int M = mp.M, Mp = mp.Mp, Mz = mp.Mz, Kc = mp.Kc, nky = mp.nky, p = P > 0 ? P : mp.win.p, P2 = 2 * p;
   const int D = mp.cheb_deg, R = mp.rows, nslot = mp.nslot;
   const int P2pad = pow2_at_least(P2), lg_pad = __builtin_ctz(P2pad);
   const int tid = threadIdx.x, nt = blockDim.x, lane = tid & (kWave - 1);
@@ -1390,7 +1707,10 @@ recip_bwd_body(gptr<const double4> __restrict__ xq, gptr<const int> __restrict__
   }
   for (int k = tid; k < 2 * P2 * (D + 1); k += nt) cv[(k / (D + 1)) * Ds + k % (D + 1)] = wcoef[k];
   if (tid == 0) *s_n = 0;
+  const ctab<T> tab = (ctab<T>)(wcoef + 2 * P2 * (D + 1));  // (half-width 4)
+  const TouchRows<T> touch(tab, P == 4 ? (sizeof(T) == 8 ? D / 2 + 1 : D + 1) : 0);
   const int total = plane_bins(x0, M, p, xcnt, mp.xcap, pre, bcell);  // synchronises
+  if constexpr (P == 4) touch.done();
   // When the plane's charges fit one stage (one per thread), their loads are
   // issued now and complete under the transforms below.
   const bool early = total <= mp.stage && total <= nt;
@@ -1455,6 +1775,13 @@ recip_bwd_body(gptr<const double4> __restrict__ xq, gptr<const int> __restrict__
       }
       __syncthreads();
       lds_fft<T>(plane, plane + Mp, 2 * Mp, nr / 2, mp.fft, twr, twi, true);
+      if constexpr (P == 4) {  // the rows' first seven columns again past the mesh
+        for (int k = tid; k < nr * 7; k += nt) {
+          T *row = plane + (size_t)(k / 7) * Mp;
+          row[M + k % 7] = row[k % 7];
+        }
+        __syncthreads();
+      }
 
       const int chunk = r0 / R;
       for (int e0 = 0; e0 < total; e0 += mp.stage) {
@@ -1465,6 +1792,14 @@ recip_bwd_body(gptr<const double4> __restrict__ xq, gptr<const int> __restrict__
       const int cnt = early ? nstaged
                             : stage_plane_charges(e0, (total - e0) < mp.stage ? (total - e0) : mp.stage, P2, pre,
                                                   bcell, xslot, mp.xcap, xq, wpart, mp.bparts, s_c, s_jb, s_n);
+      if constexpr (P == 4) {
+        if (4 * cnt <= nt)
+          gather8<T, IK, 4>(mp, tab, cv, cd, Ds, s_c, s_jb, cnt, r0, nr, chunk, comp, plane, part);
+        else if (2 * cnt <= nt)
+          gather8<T, IK, 2>(mp, tab, cv, cd, Ds, s_c, s_jb, cnt, r0, nr, chunk, comp, plane, part);
+        else
+          gather8<T, IK, 1>(mp, tab, cv, cd, Ds, s_c, s_jb, cnt, r0, nr, chunk, comp, plane, part);
+      } else {
       const int items = ((cnt * P2pad + kWave - 1) / kWave) * kWave;
       for (int it = tid; it < items; it += nt) {
         const int e = it >> lg_pad, sy = it & (P2pad - 1);
@@ -1580,6 +1915,7 @@ recip_bwd_body(gptr<const double4> __restrict__ xq, gptr<const int> __restrict__
           }
         }
       }
+      }
       if (!early) __syncthreads();  // the next batch restages the charges
       }
       __syncthreads();  // the next chunk overwrites the plane
@@ -1587,14 +1923,14 @@ recip_bwd_body(gptr<const double4> __restrict__ xq, gptr<const int> __restrict__
   }
 }
 
-template <typename T, bool IK>
+template <typename T, bool IK, int P>
 __global__ void __launch_bounds__(kPassThreads)
 k_recip_bwd(const double4 *__restrict__ xq, const int *__restrict__ xcnt, const int *__restrict__ xslot,
             const T *__restrict__ wcoef, const DevScalars *__restrict__ sc, MeshParams mp,
             const typename CplxOf<T>::type *__restrict__ tw,
             const typename CplxOf<T>::type *__restrict__ gzy, const typename CplxOf<T>::type *__restrict__ gzx,
             double4 *part) {
-  recip_bwd_body<T, IK>(to_g(xq), to_g(xcnt), to_g(xslot), to_g(wcoef), to_g(sc), mp, to_g(tw), to_g(gzy),
+  recip_bwd_body<T, IK, P>(to_g(xq), to_g(xcnt), to_g(xslot), to_g(wcoef), to_g(sc), mp, to_g(tw), to_g(gzy),
                         to_g(gzx), to_g(part), blockIdx.x % mp.M, blockIdx.x / mp.M);
 }
 
@@ -1680,12 +2016,12 @@ template <> struct MemberTables<float> {
   static __device__ const float2 *tw(const ComputeBuffers &b) { return b.tw32; }
 };
 
-template <typename T>
+template <typename T, int P>
 __global__ void __launch_bounds__(kPassThreads)
 kb_recip_fwd(const BatchMember *__restrict__ mem, const int2 *__restrict__ map) {
   const int2 w = map[blockIdx.x];
   const BatchMember &m = mem[w.x];
-  recip_fwd_body<T>(to_g(m.buf.xq), to_g(m.buf.xcnt), to_g(m.buf.xslot), to_g(MemberTables<T>::wcoef(m.buf)),
+  recip_fwd_body<T, P>(to_g(m.buf.xq), to_g(m.buf.xcnt), to_g(m.buf.xslot), to_g(MemberTables<T>::wcoef(m.buf)),
                     to_g(m.buf.sc), m.cfg.mesh, to_g(MemberTables<T>::tw(m.buf)),
                     to_g(reinterpret_cast<longlong2 *>(m.buf.gzy)), w.y % m.cfg.mesh.M, w.y / m.cfg.mesh.M);
 }
@@ -1702,13 +2038,13 @@ kb_recip_x(const BatchMember *__restrict__ mem, const int2 *__restrict__ map) {
                   to_g(reinterpret_cast<C *>(m.buf.gzx)), to_g(m.buf.epart), w.y);
 }
 
-template <typename T, bool IK>
+template <typename T, bool IK, int P>
 __global__ void __launch_bounds__(kPassThreads)
 kb_recip_bwd(const BatchMember *__restrict__ mem, const int2 *__restrict__ map) {
   using C = typename CplxOf<T>::type;
   const int2 w = map[blockIdx.x];
   const BatchMember &m = mem[w.x];
-  recip_bwd_body<T, IK>(to_g(m.buf.xq), to_g(m.buf.xcnt), to_g(m.buf.xslot), to_g(MemberTables<T>::wcoef(m.buf)),
+  recip_bwd_body<T, IK, P>(to_g(m.buf.xq), to_g(m.buf.xcnt), to_g(m.buf.xslot), to_g(MemberTables<T>::wcoef(m.buf)),
                     to_g(m.buf.sc), m.cfg.mesh, to_g(MemberTables<T>::tw(m.buf)),
                     to_g(reinterpret_cast<const C *>((const char *)m.buf.gzy + spectrum_h_offset(m.cfg.mesh))),
                     to_g(reinterpret_cast<const C *>(m.buf.gzx)), to_g(m.buf.part), w.y % m.cfg.mesh.M,
@@ -1746,12 +2082,14 @@ hipError_t launch_batch_real(const BatchMember *mem, const int2 *map, int nmap, 
   return hipGetLastError();
 }
 
-template <typename T>
+// half-width 4 takes the kernels with the lane-per-charge window, other
+// half-widths the general ones
+template <typename T, int P>
 static void launch_batch_mesh(const BatchMember *mem, int ik, const int2 *fwd, int nfwd, const int2 *x, int nx,
                               const int2 *bwd, int nbwd, size_t lds_fwd, size_t lds_x, size_t lds_bwd, int tp,
                               int tx, hipStream_t st, KernelTimer *tm) {
   if (tm) tm->before(5, st);
-  if (nfwd > 0) hipLaunchKernelGGL(kb_recip_fwd<T>, dim3(nfwd), dim3(tp), lds_fwd, st, mem, fwd);
+  if (nfwd > 0) hipLaunchKernelGGL(HIP_KERNEL_NAME(kb_recip_fwd<T, P>), dim3(nfwd), dim3(tp), lds_fwd, st, mem, fwd);
   if (tm) tm->after(5, st);
   if (tm) tm->before(6, st);
   if (nx > 0) hipLaunchKernelGGL(kb_recip_x<T>, dim3(nx), dim3(tx), lds_x, st, mem, x);
@@ -1759,24 +2097,21 @@ static void launch_batch_mesh(const BatchMember *mem, int ik, const int2 *fwd, i
   if (tm) tm->before(7, st);
   if (nbwd > 0) {
     if (ik)
-      hipLaunchKernelGGL(HIP_KERNEL_NAME(kb_recip_bwd<T, true>), dim3(nbwd), dim3(tp), lds_bwd, st, mem, bwd);
+      hipLaunchKernelGGL(HIP_KERNEL_NAME(kb_recip_bwd<T, true, P>), dim3(nbwd), dim3(tp), lds_bwd, st, mem, bwd);
     else
-      hipLaunchKernelGGL(HIP_KERNEL_NAME(kb_recip_bwd<T, false>), dim3(nbwd), dim3(tp), lds_bwd, st, mem, bwd);
+      hipLaunchKernelGGL(HIP_KERNEL_NAME(kb_recip_bwd<T, false, P>), dim3(nbwd), dim3(tp), lds_bwd, st, mem, bwd);
   }
   if (tm) tm->after(7, st);
 }
 
-hipError_t launch_batch_recip(const BatchMember *mem, int precision, int ik, const int2 *fwd, int nfwd,
+hipError_t launch_batch_recip(const BatchMember *mem, int precision, int ik, bool p4, const int2 *fwd, int nfwd,
                               const int2 *x, int nx, const int2 *bwd, int nbwd, size_t lds_fwd, size_t lds_x,
                               size_t lds_bwd, int pass_threads, int x_threads, hipStream_t st, KernelTimer *tm) {
   if (pass_threads < 1 || pass_threads > kPassThreads || x_threads < 1 || x_threads > kPassThreads)
     return hipErrorInvalidValue;
-  if (precision == 0)
-    launch_batch_mesh<double>(mem, ik, fwd, nfwd, x, nx, bwd, nbwd, lds_fwd, lds_x, lds_bwd, pass_threads,
-                              x_threads, st, tm);
-  else
-    launch_batch_mesh<float>(mem, ik, fwd, nfwd, x, nx, bwd, nbwd, lds_fwd, lds_x, lds_bwd, pass_threads,
-                             x_threads, st, tm);
+  const auto f = precision == 0 ? (p4 ? launch_batch_mesh<double, 4> : launch_batch_mesh<double, 0>)
+                                : (p4 ? launch_batch_mesh<float, 4> : launch_batch_mesh<float, 0>);
+  f(mem, ik, fwd, nfwd, x, nx, bwd, nbwd, lds_fwd, lds_x, lds_bwd, pass_threads, x_threads, st, tm);
   return hipGetLastError();
 }
 
@@ -1805,7 +2140,8 @@ void mesh_lds_bytes(const MeshParams &m, int precision, size_t *fwd, size_t *x, 
   *bwd = rows_t + zp + tw + misc;
 }
 
-bool mesh_choose_rows(MeshParams &m, int precision, size_t max_lds) {
+// With m.Mp given.
+static bool choose_rows(MeshParams &m, int precision, size_t max_lds) {
   for (int nchunk = 1; nchunk <= m.M / 2; ++nchunk) {
     int rows = (m.M + nchunk - 1) / nchunk;
     rows += rows & 1;
@@ -1833,33 +2169,39 @@ bool mesh_choose_rows(MeshParams &m, int precision, size_t max_lds) {
   return false;
 }
 
-hipError_t configure_kernels(size_t max_lds) {
-  const int v = (int)max_lds;
-  hipError_t e;
-  e = hipFuncSetAttribute((const void *)k_recip_fwd<double>, hipFuncAttributeMaxDynamicSharedMemorySize, v);
-  if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute((const void *)k_recip_fwd<float>, hipFuncAttributeMaxDynamicSharedMemorySize, v);
-  if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute((const void *)k_recip_x<double>, hipFuncAttributeMaxDynamicSharedMemorySize, v);
+bool mesh_choose_rows(MeshParams &m, int precision, size_t max_lds) {
+  m.Mp = mesh_stride(m.M, m.win.p);
+  if (choose_rows(m, precision, max_lds)) return true;
+  // an LDS budget that only the general kernels' narrower rows meet
+  if (m.Mp == m.M + 1) return false;
+  m.Mp = m.M + 1;
+  return choose_rows(m, precision, max_lds);
+}
 
-  if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute((const void *)k_recip_x<float>, hipFuncAttributeMaxDynamicSharedMemorySize, v);
-  if (e != hipSuccess) return e;
-  const void *more[] = {(const void *)k_recip_bwd<double, false>,  (const void *)k_recip_bwd<float, false>,
-                        (const void *)k_recip_bwd<double, true>,   (const void *)k_recip_bwd<float, true>,
-                        (const void *)kb_recip_fwd<double>,        (const void *)kb_recip_fwd<float>,
-                        (const void *)kb_recip_x<double>,          (const void *)kb_recip_x<float>,
-                        (const void *)kb_recip_bwd<double, false>, (const void *)kb_recip_bwd<float, false>,
-                        (const void *)kb_recip_bwd<double, true>,  (const void *)kb_recip_bwd<float, true>};
-  const void *const *batched = more;
-  for (size_t k = 0; k < sizeof(more) / sizeof(more[0]); ++k) {
-    e = hipFuncSetAttribute(batched[k], hipFuncAttributeMaxDynamicSharedMemorySize, v);
+hipError_t configure_kernels(size_t max_lds) {
+  const void *const all[] = {
+      (const void *)k_recip_fwd<double, 0>,         (const void *)k_recip_fwd<float, 0>,
+      (const void *)k_recip_fwd<double, 4>,         (const void *)k_recip_fwd<float, 4>,
+      (const void *)k_recip_x<double>,              (const void *)k_recip_x<float>,
+      (const void *)k_recip_bwd<double, false, 0>,  (const void *)k_recip_bwd<float, false, 0>,
+      (const void *)k_recip_bwd<double, true, 0>,   (const void *)k_recip_bwd<float, true, 0>,
+      (const void *)k_recip_bwd<double, false, 4>,  (const void *)k_recip_bwd<float, false, 4>,
+      (const void *)k_recip_bwd<double, true, 4>,   (const void *)k_recip_bwd<float, true, 4>,
+      (const void *)kb_recip_fwd<double, 0>,        (const void *)kb_recip_fwd<float, 0>,
+      (const void *)kb_recip_fwd<double, 4>,        (const void *)kb_recip_fwd<float, 4>,
+      (const void *)kb_recip_x<double>,             (const void *)kb_recip_x<float>,
+      (const void *)kb_recip_bwd<double, false, 0>, (const void *)kb_recip_bwd<float, false, 0>,
+      (const void *)kb_recip_bwd<double, true, 0>,  (const void *)kb_recip_bwd<float, true, 0>,
+      (const void *)kb_recip_bwd<double, false, 4>, (const void *)kb_recip_bwd<float, false, 4>,
+      (const void *)kb_recip_bwd<double, true, 4>,  (const void *)kb_recip_bwd<float, true, 4>};
+  for (const void *k : all) {
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
-template <typename T>
+template <typename T, int P>
 static void launch_mesh(const ComputeConfig &cfg, const ComputeBuffers &b, hipStream_t st, KernelTimer *tm,
                         int x_threads) {
   using C = typename CplxOf<T>::type;
@@ -1870,7 +2212,7 @@ static void launch_mesh(const ComputeConfig &cfg, const ComputeBuffers &b, hipSt
   C *gh = reinterpret_cast<C *>((char *)b.gzy + spectrum_h_offset(mp));  // field spectrum
   const int nplane = mp.M * mp.parts;
   if (tm) tm->before(5, st);
-  hipLaunchKernelGGL(k_recip_fwd<T>, dim3(nplane), dim3(kPassThreads), cfg.lds_fwd, st, (const double4 *)b.xq,
+  hipLaunchKernelGGL(HIP_KERNEL_NAME(k_recip_fwd<T, P>), dim3(nplane), dim3(kPassThreads), cfg.lds_fwd, st, (const double4 *)b.xq,
                      (const int *)b.xcnt, (const int *)b.xslot, wc, (const DevScalars *)b.sc, mp, tw, gfx);
   if (tm) tm->after(5, st);
   if (tm) tm->before(6, st);
@@ -1879,11 +2221,11 @@ static void launch_mesh(const ComputeConfig &cfg, const ComputeBuffers &b, hipSt
   if (tm) tm->after(6, st);
   if (tm) tm->before(7, st);
   if (mp.ik)
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_recip_bwd<T, true>), dim3(mp.M * mp.bparts), dim3(kPassThreads), cfg.lds_bwd, st,
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_recip_bwd<T, true, P>), dim3(mp.M * mp.bparts), dim3(kPassThreads), cfg.lds_bwd, st,
                        (const double4 *)b.xq, (const int *)b.xcnt, (const int *)b.xslot, wc,
                        (const DevScalars *)b.sc, mp, tw, (const C *)gh, (const C *)b.gzx, b.part);
   else
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_recip_bwd<T, false>), dim3(mp.M * mp.bparts), dim3(kPassThreads), cfg.lds_bwd, st,
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_recip_bwd<T, false, P>), dim3(mp.M * mp.bparts), dim3(kPassThreads), cfg.lds_bwd, st,
                        (const double4 *)b.xq, (const int *)b.xcnt, (const int *)b.xslot, wc,
                        (const DevScalars *)b.sc, mp, tw, (const C *)gh, (const C *)b.gzx, b.part);
   if (tm) tm->after(7, st);
@@ -1933,10 +2275,10 @@ hipError_t launch_recip(const ComputeConfig &cfg, const ComputeBuffers &b, int64
   int tx = x_threads < kWave ? kWave : (x_threads > kPassThreads ? kPassThreads : x_threads);
   while (tx < fft_max_butterflies(cfg.mesh.fft) && tx < kPassThreads) tx *= 2;
   if (tx > kPassThreads) tx = kPassThreads;
-  if (cfg.precision == 0)
-    launch_mesh<double>(cfg, b, st, tm, tx);
-  else
-    launch_mesh<float>(cfg, b, st, tm, tx);
+  const bool p4 = mesh_win8(cfg.mesh);
+  const auto f = cfg.precision == 0 ? (p4 ? launch_mesh<double, 4> : launch_mesh<double, 0>)
+                                    : (p4 ? launch_mesh<float, 4> : launch_mesh<float, 0>);
+  f(cfg, b, st, tm, tx);
   return hipGetLastError();
 }
 

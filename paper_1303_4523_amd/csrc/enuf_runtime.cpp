@@ -309,6 +309,42 @@ int cached_window_series(const WindowParams &w, int fp32, std::vector<long doubl
   return it->second.D;
 }
 
+// Append the rows that the kernels of half-width 4 read (window8) to the
+// series [value, derivative][8][D + 1].  FP32: row k holds coefficient k of the
+// 8 value and the 8 derivative series.  FP64: the even and odd parts of series
+// 0 .. 3 as polynomials in x^2, highest power first: row k holds the
+// coefficients of x^{2m} of E and of x^{2m + 1} of O, m = D/2 - k, for the
+// values, then for the derivatives (series 7 - s mirrors series s).
+void window8_rows(int fp32, int D, std::vector<long double> *coef) {
+  const std::vector<long double> c(*coef);
+  if (fp32) {
+    for (int k = 0; k <= D; ++k)
+      for (int i = 0; i < 16; ++i) coef->push_back(c[(size_t)i * (D + 1) + k]);
+    return;
+  }
+  // Chebyshev to powers of x
+  std::vector<long double> mono((size_t)16 * (D + 1), 0.0L);
+  std::vector<long double> t0(D + 1, 0.0L), t1(D + 1, 0.0L), t2(D + 1, 0.0L);
+  t0[0] = 1.0L;
+  if (D >= 1) t1[1] = 1.0L;
+  for (int k = 0; k <= D; ++k) {
+    const std::vector<long double> &t = k == 0 ? t0 : t1;
+    for (int i = 0; i < 16; ++i)
+      for (int m = 0; m <= D; ++m) mono[(size_t)i * (D + 1) + m] += c[(size_t)i * (D + 1) + k] * t[m];
+    if (k >= 1) {
+      for (int m = 0; m <= D; ++m) t2[m] = (m > 0 ? 2.0L * t1[m - 1] : 0.0L) - t0[m];
+      t0 = t1;
+      t1 = t2;
+    }
+  }
+  for (int m = D / 2; m >= 0; --m)
+    for (int half = 0; half < 4; ++half)  // E, O of the values, E, O of the derivatives
+      for (int s = 0; s < 4; ++s) {
+        const int power = 2 * m + (half & 1), i = (half >> 1) * 8 + s;
+        coef->push_back(power <= D ? mono[(size_t)i * (D + 1) + power] : 0.0L);
+      }
+}
+
 // Device layout of the window series for one precision: value series and
 // derivative series, both at stride D + 1 (the derivative's last coefficient
 // 0).  Returns the degree D.
@@ -322,6 +358,7 @@ int window_table(const WindowParams &w, int fp32, std::vector<long double> *coef
     for (int k = 0; k < D; ++k)
       (*coef)[(size_t)(P2 + s) * (D + 1) + k] = fit[(size_t)P2 * (D + 1) + (size_t)s * D + k];
   }
+  if (w.p == 4) window8_rows(fp32, D, coef);
   return D;
 }
 
@@ -445,7 +482,7 @@ bool plan_geometry(int64_t N, double box, int p, int M, int Kc, double r_cut, si
   g->nblk = (int)((N + kPrepThreads - 1) / kPrepThreads);
   // the gather partials are sized for the largest series degree in either precision
   MeshParams m{};
-  m.M = M; m.Mp = M + 1; m.Mz = M + 1; m.Kc = Kc; m.nky = 2 * Kc - 1;
+  m.M = M; m.Mp = mesh_stride(M, p); m.Mz = M + 1; m.Kc = Kc; m.nky = 2 * Kc - 1;
   m.win.p = p;
   m.cheb_deg = kMaxChebDeg;
   g->part_slots = 0;
@@ -481,8 +518,8 @@ std::array<size_t, kPlanBuffers> plan_buffer_bytes(int64_t N, int p, int M, int 
           nblk * sizeof(double),                              // blk_eg
           2 * (size_t)M * kXSub * sizeof(int),                // xcnt (two sets)
           (size_t)M * kXSub * (size_t)g.xcap * sizeof(int),   // xslot
-          P2 * (2 * kMaxChebDeg + 2) * sizeof(double),        // wcoef64
-          P2 * (2 * kMaxChebDeg + 2) * sizeof(float),         // wcoef32
+          window_entries(p, kMaxChebDeg) * sizeof(double),    // wcoef64
+          window_entries(p, kMaxChebDeg) * sizeof(float),     // wcoef32
           nky * sizeof(double),                               // atab
           (size_t)M * sizeof(double2),                        // tw64
           (size_t)M * sizeof(float2)};                        // tw32
@@ -551,7 +588,7 @@ bool plan_config(int64_t N, double box, double alpha, int p, double sigma, int M
   c.L = box; c.alpha = alpha; c.r_cut = r_cut; c.lambda = lambda;
   c.precision = ENUF_FP64;
   MeshParams &m = c.mesh;
-  m.M = M; m.Mp = M + 1; m.Mz = M + 1; m.Kc = Kc; m.nky = 2 * Kc - 1;
+  m.M = M; m.Mp = mesh_stride(M, p); m.Mz = M + 1; m.Kc = Kc; m.nky = 2 * Kc - 1;
   m.L = box; m.m_over_l = (double)M / box;
   m.win = make_window(ENUF_WINDOW_KB, p, sigma);
   m.fft = fp;
@@ -760,6 +797,7 @@ int enuf_plan_set_options(enuf_plan *plan, int precision, int window) {
     plan->cfg.precision = old_prec;
     plan->cfg.mesh.win = make_window(old_win, plan->p, plan->sigma);
     (void)upload_tables(plan);
+    plan->cfg.mesh.Mp = old_mesh.Mp;
     plan->cfg.mesh.rows = old_mesh.rows;
     plan->cfg.mesh.nchunk = old_mesh.nchunk;
     plan->cfg.mesh.nslot = old_mesh.nslot;
@@ -1717,6 +1755,7 @@ struct enuf_batch {
   int concurrent = 1;
   int use_graph = 1;
   int ik = -1;       // force mode of the members (all alike; -1 while empty)
+  bool p4 = false;   // mesh_win8 of every member
   std::vector<Member> members;
   int next_id = 0;
   // device copies of the member table and the work maps (rebuilt when the
@@ -1838,6 +1877,7 @@ int batch_rebuild(enuf_batch *b) {
   std::vector<int2> map[7];
   size_t lf = 0, lx = 0, lb = 0;
   int tp = b->tune.pass_threads, tx = b->tune.x_threads;  // enough threads for every member's FFT passes
+  bool p4 = true;
   for (int k : order) {
     const BatchMember m = member_view(b->members[k], b->tune, 0);
     const int id = (int)mem.size();
@@ -1849,6 +1889,7 @@ int batch_rebuild(enuf_batch *b) {
                            bplanes, m.nblk};
     for (int s = 0; s < 7; ++s)
       for (int i = 0; i < counts[s]; ++i) map[s].push_back(make_int2(id, i));
+    p4 = p4 && mesh_win8(m.cfg.mesh);
     lf = std::max(lf, m.cfg.lds_fwd);
     lx = std::max(lx, m.cfg.lds_x);
     lb = std::max(lb, m.cfg.lds_bwd);
@@ -1901,6 +1942,7 @@ int batch_rebuild(enuf_batch *b) {
   b->lds_fwd = lf;
   b->lds_x = lx;
   b->lds_bwd = lb;
+  b->p4 = p4;
   b->pass_threads = tp;
   b->x_threads = tx;
   b->drop_graph();
@@ -1935,7 +1977,7 @@ hipError_t batch_forces(enuf_batch *b, const BatchMember *mt, bool fork, int ene
   if (tm) tm->after(ENUF_K_REAL, s1);
   if (fork && e == hipSuccess) e = hipEventRecord(b->join_ev[1], s1);
   if (e == hipSuccess)
-    e = launch_batch_recip(mt, b->precision, b->ik, mp + o[3], o[4] - o[3], mp + o[4], o[5] - o[4],
+    e = launch_batch_recip(mt, b->precision, b->ik, b->p4, mp + o[3], o[4] - o[3], mp + o[4], o[5] - o[4],
                            mp + o[5], o[6] - o[5], b->lds_fwd, b->lds_x, b->lds_bwd, b->pass_threads,
                            b->x_threads, st, tm);
   if (fork)
