@@ -121,6 +121,11 @@ hipError_t launch_dpd_pair(int64_t N, const DpdParams &P, uint64_t step, const d
                            const double4 *cpos, const double4 *cvel, const int *bond_start, const int *bond_to,
                            double *fdpd, hipStream_t st, KernelTimer *tm = nullptr,
                            const unsigned long long *step_dev = nullptr);
+// The pair forces and the real-space term (launch_real) in one launch.
+hipError_t launch_dpd_pair_real(const DpdParams &P, uint64_t step, const double *pos, const int *dcnt,
+                                const double4 *cpos, const double4 *cvel, const int *bond_start, const int *bond_to,
+                                double *fdpd, const ComputeConfig &cfg, const ComputeBuffers &b, int64_t nq_max,
+                                int energies, hipStream_t st, const unsigned long long *step_dev);
 // The combine kernel of a DPD step fused with the next step's pre kernel
 // (no energy reduction: fa.energies must be 0, else hipErrorInvalidValue).
 hipError_t launch_combine_pre(const ComputeConfig &cfg, const ComputeBuffers &b, double *forces,

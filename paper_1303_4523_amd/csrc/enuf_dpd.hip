@@ -9,6 +9,7 @@
 #include "enuf_device.h"
 #include "enuf_dpd.h"
 #include "enuf_combine.h"
+#include "enuf_real.h"
 
 namespace enuf {
 
@@ -630,6 +631,40 @@ k_dpd_pair(DpdParams P, uint64_t step, const unsigned long long *step_dev, const
                         to_g(cvel), to_g(bond_start), to_g(bond_to), to_g(fdpd), blockIdx.x, gridDim.x);
 }
 
+// The same with the real-space term of the charges in the launch's last
+// `real.blocks` work-groups: both need only the pre kernel's bins, and as
+// launches of their own the second one's start, its few work-groups and its
+// tail came after the first, on the longest path of a small step (20 steps of
+// 24000 particles 1383 -> 1165 us, 11 of 3333 particles 647 -> 616 us).  The
+// real-space work-groups use the pair stage's LDS.
+struct RealArgs {
+  const double4 *xq;
+  const int *ccnt;
+  const double4 *cgrid;
+  const int *cidx;
+  CellParams cells;
+  double L, alpha, rc2, lambda;
+  DevScalars *sc;
+  unsigned long long *freal, *ereal;
+  int energies, blocks;
+};
+static_assert(kRealThreads == kPairThreads, "one launch");
+__global__ void __launch_bounds__(kPairThreads)
+k_dpd_pair_real(DpdParams P, uint64_t step, const unsigned long long *step_dev, const double *__restrict__ pos,
+                const int *__restrict__ dcnt, const double4 *__restrict__ cpos, const double4 *__restrict__ cvel,
+                const int *__restrict__ bond_start, const int *__restrict__ bond_to, double *__restrict__ fdpd,
+                RealArgs real) {
+  extern __shared__ __align__(32) unsigned char pair_real_smem[];
+  const int npair = (int)gridDim.x - real.blocks, b = (int)blockIdx.x;
+  if (b < npair)
+    dpd_pair_body<kPairU, true>(P, step_dev ? (uint64_t)*step_dev : step, to_g(pos), to_g(dcnt), to_g(cpos),
+                                to_g(cvel), to_g(bond_start), to_g(bond_to), to_g(fdpd), b, npair);
+  else
+    real_body(to_g(real.xq), to_g(real.ccnt), to_g(real.cgrid), to_g(real.cidx), real.cells, real.L, real.alpha,
+              real.rc2, real.lambda, to_g(real.sc), to_g(real.freal), to_g(real.ereal), real.energies,
+              *reinterpret_cast<RealShared *>(pair_real_smem), b - npair, real.blocks);
+}
+
 void pair_segments(int n, int target, int *seg_cells, int *nseg) {
   target = target < 1 ? 1 : (target > kPairSegMax ? kPairSegMax : target);
   *nseg = (n + target - 1) / target;
@@ -793,6 +828,9 @@ constexpr size_t kBatchPairLdsBytes = (size_t)kBatchPairStage * (sizeof(double4)
 hipError_t configure_pair_kernels(size_t lds_bytes) {
   const int v = (int)(lds_bytes > kPairLdsBytes ? lds_bytes : kPairLdsBytes);
   hipError_t e = hipFuncSetAttribute((const void *)k_dpd_pair, hipFuncAttributeMaxDynamicSharedMemorySize, v);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute((const void *)k_dpd_pair_real, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            v > (int)sizeof(RealShared) ? v : (int)sizeof(RealShared));
   const void *k[] = {(const void *)kb_dpd_pair<4>, (const void *)kb_dpd_pair<8>};
   for (const void *f : k)
     if (e == hipSuccess)
@@ -851,6 +889,19 @@ hipError_t launch_dpd_pair(int64_t N, const DpdParams &P, uint64_t step, const d
   hipLaunchKernelGGL(k_dpd_pair, dim3(nb), dim3(kPairThreads), pair_lds_bytes(P, true), st, P, step, step_dev, pos,
                      dcnt, cpos, cvel, bond_start, bond_to, fdpd);
   if (tm) tm->after(1, st);
+  return hipGetLastError();
+}
+
+hipError_t launch_dpd_pair_real(const DpdParams &P, uint64_t step, const double *pos, const int *dcnt,
+                                const double4 *cpos, const double4 *cvel, const int *bond_start, const int *bond_to,
+                                double *fdpd, const ComputeConfig &cfg, const ComputeBuffers &b, int64_t nq_max,
+                                int energies, hipStream_t st, const unsigned long long *step_dev) {
+  const RealArgs real = {b.xq, b.ccnt, b.cgrid, b.cidx, cfg.cells, cfg.L, cfg.alpha, cfg.r_cut * cfg.r_cut,
+                         cfg.lambda, b.sc, b.freal, b.ereal, energies, real_blocks(cfg.cells, nq_max, kRealDpdBlocks)};
+  const size_t lds = pair_lds_bytes(P, true);
+  hipLaunchKernelGGL(k_dpd_pair_real, dim3(pair_blocks(P) + real.blocks), dim3(kPairThreads),
+                     lds > sizeof(RealShared) ? lds : sizeof(RealShared), st, P, step, step_dev, pos, dcnt, cpos,
+                     cvel, bond_start, bond_to, fdpd, real);
   return hipGetLastError();
 }
 

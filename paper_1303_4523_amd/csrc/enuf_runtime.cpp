@@ -1417,8 +1417,8 @@ static hipError_t capture_tail(hipStream_t st, hipGraphNode_t *node, size_t *cou
 //         and advanced in device memory; the fork and join are dependency
 //         edges of the capture instead of events).
 // With a plan, the mesh passes (the longest chain) are enqueued first on the
-// integrator's stream; the pair forces and then the real-space term run on
-// one forked stream beside them (a second forked stream costs more in
+// integrator's stream; the pair forces and the real-space term run on
+// one forked stream beside them, in one launch (a second forked stream costs more in
 // cross-stream waits than it gains); the combine kernel joins the two.  All
 // cell and bin counts come in two sets, step k using set k mod 2, so that the
 // fused combine can clear step k's set while it bins step k + 1 into the
@@ -1472,11 +1472,16 @@ static int dpd_eval(enuf_dpd *d, int mode, double *pos, double *vel, double *for
     // the pair forces and the real-space term depend on the pre kernel only
     if (graph && fork && e == hipSuccess)
       e = hipStreamUpdateCaptureDependencies(st, &n_pre, c_pre, hipStreamSetCaptureDependencies);
-    if (e == hipSuccess)
-      e = launch_dpd_pair(N, d->P, step, pos, dcnt, d->cpos, d->cvel, d->bond_start, d->bond_to,
-                          d->fdpd, s1, tm, step_dev);
     const int ndcell3 = d->P.ncell * d->P.ncell * d->P.ncell;
-    if (e == hipSuccess) e = launch_real(pl->cfg, bk, d->nq, energies ? 1 : 0, s1, tm);
+    if (tm) {  // the stage timers take them one by one
+      if (e == hipSuccess)
+        e = launch_dpd_pair(N, d->P, step, pos, dcnt, d->cpos, d->cvel, d->bond_start, d->bond_to,
+                            d->fdpd, s1, tm, step_dev);
+      if (e == hipSuccess) e = launch_real(pl->cfg, bk, d->nq, energies ? 1 : 0, s1, tm);
+    } else if (e == hipSuccess) {
+      e = launch_dpd_pair_real(d->P, step, pos, dcnt, d->cpos, d->cvel, d->bond_start, d->bond_to, d->fdpd,
+                               pl->cfg, bk, d->nq, energies ? 1 : 0, s1, step_dev);
+    }
     if (events && e == hipSuccess) e = hipEventRecord(d->join_ev, s1);
     if (events && e == hipSuccess) e = hipStreamWaitEvent(st, d->join_ev, 0);
     // the combine kernel depends on the mesh passes and the real-space term
