@@ -13,6 +13,11 @@ namespace enuf {
 namespace {
 
 constexpr int kHistTile = 256;         // selected particles per tile (one per thread)
+// Work-groups to aim for, and slices of a j tile at most.  Up to about 45 tiles
+// the tile pairs alone leave CUs idle (4000 particles: 42 us in 272 work-groups,
+// 35 in 544, 33 in 1088); each further slice adds a histogram to be cleared and
+// summed.
+constexpr int kHistBlocks = 1024, kHistSlices = 8;
 
 // Minimum-image component v - L rint(v / L) with no fused multiply-add, so
 // that the squared distance (and so the bin) is the one a plain IEEE FP64
@@ -34,26 +39,37 @@ __device__ __forceinline__ double edge2(int k, double w) {
   return e * e;
 }
 
-// One block per (i tile, j tile) with j tile >= i tile: the j tile's
+// The same with 1 / L at hand: the quotient and its exact remainder give the
+// correctly rounded v / L (three multiply-adds instead of a division; where
+// the remainder underflows the quotient rounds to 0 either way).
+__device__ __forceinline__ double min_image_by(double v, double L, double inv_l) {
+#pragma clang fp contract(off)
+  const double q = v * inv_l;
+  return v - L * rint(fma(fma(-q, L, v), inv_l, q));
+}
+
+// One block per (i tile, slice of a j tile) with j tile >= i tile: the slice's
 // positions and classes are staged in LDS, each thread takes one i and walks
-// the tile (j > i within the diagonal tile), and counts go to a block-private
+// the slice (j > i within the diagonal tile), and counts go to a block-private
 // LDS histogram that is added to the global one at the end.  The bin is
 // decided on r^2 against the squared bin edges (k w)^2, so it is independent
-// of how the square root of the first guess rounds.  Entries whose index or
-// class is out of range are skipped.
+// of how the first guess, in FP32, rounds.  Entries whose index or class is
+// out of range are skipped.  Bound by FP64 issue and the LDS atomics; three
+// divisions, an FP64 square root and division and the bin search's loops in every
+// pair made it 193 us at 4000 particles in 136 work-groups, against 33.
 __global__ void __launch_bounds__(kHistTile)
 k_pair_histogram(const double *__restrict__ pos, int64_t n, int64_t nsel, const int64_t *__restrict__ sel,
                  const int *__restrict__ cls, int ncls, double L, double w, int nbins,
                  unsigned long long *__restrict__ hist) {
-  const int ti = blockIdx.y, tj = blockIdx.x;
+  const int ti = blockIdx.y, tj = blockIdx.x, slice = kHistTile / gridDim.z, js = blockIdx.z * slice;
   if (tj < ti) return;  // whole block leaves before any barrier
   extern __shared__ unsigned int s_hist[];
   __shared__ double s_x[kHistTile], s_y[kHistTile], s_z[kHistTile];
   __shared__ int s_c[kHistTile];
   const int nh = ncls * ncls * nbins;
   for (int k = threadIdx.x; k < nh; k += blockDim.x) s_hist[k] = 0u;
-  {
-    const int64_t b = (int64_t)tj * kHistTile + threadIdx.x;
+  if ((int)threadIdx.x < slice) {
+    const int64_t b = (int64_t)tj * kHistTile + js + threadIdx.x;
     int c = -1;
     double x = 0.0, y = 0.0, z = 0.0;
     if (b < nsel) {
@@ -86,20 +102,31 @@ k_pair_histogram(const double *__restrict__ pos, int64_t n, int64_t nsel, const 
     }
   }
   if (ci >= 0) {
-    const double emax = edge2(nbins, w);
-    const int j0 = (ti == tj) ? (int)threadIdx.x + 1 : 0;
-    for (int jj = j0; jj < kHistTile; ++jj) {
-      const int cj = s_c[jj];
-      if (cj < 0) continue;
-      const double dx = min_image_nofma(s_x[jj] - xi, L);
-      const double dy = min_image_nofma(s_y[jj] - yi, L);
-      const double dz = min_image_nofma(s_z[jj] - zi, L);
+    const double emax = edge2(nbins, w), inv_l = 1.0 / L;
+    const float inv_w = (float)(1.0 / w);
+    const int j0 = (ti == tj && (int)threadIdx.x + 1 > js) ? (int)threadIdx.x + 1 - js : 0;
+    // the next particle is read ahead of this one's atomic
+    double xj = s_x[0], yj = s_y[0], zj = s_z[0];
+    int cn = s_c[0];
+    for (int jj = 0; jj < slice; ++jj) {
+      const int cj = __builtin_amdgcn_readfirstlane(cn);
+      const double dx = min_image_by(xj - xi, L, inv_l);
+      const double dy = min_image_by(yj - yi, L, inv_l);
+      const double dz = min_image_by(zj - zi, L, inv_l);
       const double r2 = dist2_nofma(dx, dy, dz);
-      if (!(r2 < emax)) continue;
-      int k = (int)(sqrt(r2) / w);
-      k = k < nbins - 1 ? k : nbins - 1;
-      while (k > 0 && edge2(k, w) > r2) --k;
-      while (k < nbins - 1 && edge2(k + 1, w) <= r2) ++k;
+      const int nx = jj + 1 < slice ? jj + 1 : jj;
+      xj = s_x[nx];
+      yj = s_y[nx];
+      zj = s_z[nx];
+      cn = s_c[nx];
+      if (cj < 0 || jj < j0 || !(r2 < emax)) continue;
+      int k = (int)fminf(__builtin_amdgcn_sqrtf((float)r2) * inv_w, (float)(nbins - 1));
+      if (__builtin_expect(edge2(k, w) > r2 || edge2(k + 1, w) <= r2, 0)) {
+#pragma clang loop unroll(disable) vectorize(disable)
+        while (k > 0 && edge2(k, w) > r2) --k;
+#pragma clang loop unroll(disable) vectorize(disable)
+        while (k < nbins - 1 && edge2(k + 1, w) <= r2) ++k;
+      }
       const int lo = ci < cj ? ci : cj, hi = ci < cj ? cj : ci;
       atomicAdd(&s_hist[(lo * ncls + hi) * nbins + k], 1u);
     }
@@ -167,7 +194,9 @@ hipError_t launch_pair_histogram(const double *pos, int64_t n, int64_t nsel, con
   if (nsel < 2) return hipSuccess;
   const int64_t nt = (nsel + kHistTile - 1) / kHistTile;
   const size_t lds = (size_t)ncls * ncls * nbins * sizeof(unsigned int);
-  hipLaunchKernelGGL(k_pair_histogram, dim3((unsigned)nt, (unsigned)nt), dim3(kHistTile), lds, st, pos, n, nsel,
+  int slices = 1;
+  while (slices < kHistSlices && nt * (nt + 1) / 2 * slices < kHistBlocks) slices *= 2;
+  hipLaunchKernelGGL(k_pair_histogram, dim3((unsigned)nt, (unsigned)nt, (unsigned)slices), dim3(kHistTile), lds, st, pos, n, nsel,
                      sel, cls, ncls, box, r_max / nbins, nbins, hist);
   return hipGetLastError();
 }
