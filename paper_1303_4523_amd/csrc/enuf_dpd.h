@@ -100,9 +100,9 @@ hipError_t configure_pair_kernels(size_t lds_bytes);
 int pair_blocks(const DpdParams &P);
 hipError_t launch_batch_real(const BatchMember *mem, const int2 *map, int nmap, int energies, hipStream_t st);
 // pass_threads, x_threads: work-group sizes of the spread/gather passes and of
-// the x pass (at least fft_max_butterflies of every member).  p4: the
-// kernels of half-width 4 run (mesh_win8 of every member).
-hipError_t launch_batch_recip(const BatchMember *mem, int precision, int ik, bool p4, const int2 *fwd, int nfwd,
+// the x pass (at least fft_max_butterflies of every member).  p4: 4
+// (mesh_win8 of every member), 0 (of none) or -1 (of some).
+hipError_t launch_batch_recip(const BatchMember *mem, int precision, int ik, int p4, const int2 *fwd, int nfwd,
                               const int2 *x, int nx, const int2 *bwd, int nbwd, size_t lds_fwd, size_t lds_x,
                               size_t lds_bwd, int pass_threads, int x_threads, hipStream_t st,
                               KernelTimer *tm = nullptr);

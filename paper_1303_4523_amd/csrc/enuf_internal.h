@@ -147,10 +147,10 @@ struct MeshParams {
 // Row stride of the LDS planes, odd (no bank conflicts between rows).  The
 // stencils of half-width 4 run up to 7 columns past the mesh instead of
 // wrapping along z.
-inline int mesh_stride(int M, int p) { return p == 4 ? M + 7 : M + 1; }
+constexpr int mesh_stride(int M, int p) { return p == 4 ? M + 7 : M + 1; }
 
 // Whether the kernels of half-width 4 run (the LDS budget admits their rows).
-inline bool mesh_win8(const MeshParams &m) { return m.win.p == 4 && m.Mp == mesh_stride(m.M, 4); }
+constexpr bool mesh_win8(const MeshParams &m) { return m.win.p == 4 && m.Mp == mesh_stride(m.M, 4); }
 
 // Entries of the window tables: value and derivative series [2][2p][D + 1]
 // and, for half-width 4, the rows read by window8 (16 wide; FP64 D/2 + 1 of

@@ -1276,14 +1276,29 @@ template <> struct MemberTables<float> {
   static __device__ const float2 *tw(const ComputeBuffers &b) { return b.tw32; }
 };
 
+// The kernels of one half-width rule (4: every member takes the windows of
+// half-width 4; 0: none does), or of both, where each member takes the path it
+// takes alone (its results are bitwise the same in any batch).
+constexpr int kAnyHalf = -1;
+template <int P> struct HalfWidth { static constexpr int p = P; };
+
 template <typename T, int P>
 __global__ void __launch_bounds__(kPassThreads)
 kb_recip_fwd(const BatchMember *__restrict__ mem, const int2 *__restrict__ map) {
   const int2 w = map[blockIdx.x];
   const BatchMember &m = mem[w.x];
-  recip_fwd_body<T, P>(to_g(m.buf.xq), to_g(m.buf.xcnt), to_g(m.buf.xslot), to_g(MemberTables<T>::wcoef(m.buf)),
-                    to_g(m.buf.sc), m.cfg.mesh, to_g(MemberTables<T>::tw(m.buf)),
-                    to_g(reinterpret_cast<longlong2 *>(m.buf.gzy)), w.y % m.cfg.mesh.M, w.y / m.cfg.mesh.M);
+  auto body = [&](auto half) {
+    recip_fwd_body<T, half.p>(to_g(m.buf.xq), to_g(m.buf.xcnt), to_g(m.buf.xslot), to_g(MemberTables<T>::wcoef(m.buf)),
+                              to_g(m.buf.sc), m.cfg.mesh, to_g(MemberTables<T>::tw(m.buf)),
+                              to_g(reinterpret_cast<longlong2 *>(m.buf.gzy)), w.y % m.cfg.mesh.M,
+                              w.y / m.cfg.mesh.M);
+  };
+  if constexpr (P != kAnyHalf)
+    body(HalfWidth<P>());
+  else if (mesh_win8(m.cfg.mesh))
+    body(HalfWidth<4>());
+  else
+    body(HalfWidth<0>());
 }
 
 template <typename T>
@@ -1304,11 +1319,19 @@ kb_recip_bwd(const BatchMember *__restrict__ mem, const int2 *__restrict__ map) 
   using C = typename CplxOf<T>::type;
   const int2 w = map[blockIdx.x];
   const BatchMember &m = mem[w.x];
-  recip_bwd_body<T, IK, P>(to_g(m.buf.xq), to_g(m.buf.xcnt), to_g(m.buf.xslot), to_g(MemberTables<T>::wcoef(m.buf)),
-                    to_g(m.buf.sc), m.cfg.mesh, to_g(MemberTables<T>::tw(m.buf)),
-                    to_g(reinterpret_cast<const C *>((const char *)m.buf.gzy + spectrum_h_offset(m.cfg.mesh))),
-                    to_g(reinterpret_cast<const C *>(m.buf.gzx)), to_g(m.buf.part), w.y % m.cfg.mesh.M,
-                    w.y / m.cfg.mesh.M);
+  auto body = [&](auto half) {
+    recip_bwd_body<T, IK, half.p>(
+        to_g(m.buf.xq), to_g(m.buf.xcnt), to_g(m.buf.xslot), to_g(MemberTables<T>::wcoef(m.buf)), to_g(m.buf.sc),
+        m.cfg.mesh, to_g(MemberTables<T>::tw(m.buf)),
+        to_g(reinterpret_cast<const C *>((const char *)m.buf.gzy + spectrum_h_offset(m.cfg.mesh))),
+        to_g(reinterpret_cast<const C *>(m.buf.gzx)), to_g(m.buf.part), w.y % m.cfg.mesh.M, w.y / m.cfg.mesh.M);
+  };
+  if constexpr (P != kAnyHalf)
+    body(HalfWidth<P>());
+  else if (mesh_win8(m.cfg.mesh))
+    body(HalfWidth<4>());
+  else
+    body(HalfWidth<0>());
 }
 
 __global__ void __launch_bounds__(kPrepThreads)
@@ -1342,8 +1365,6 @@ hipError_t launch_batch_real(const BatchMember *mem, const int2 *map, int nmap, 
   return hipGetLastError();
 }
 
-// half-width 4 takes the kernels with the lane-per-charge window, other
-// half-widths the general ones
 template <typename T, int P>
 static void launch_batch_mesh(const BatchMember *mem, int ik, const int2 *fwd, int nfwd, const int2 *x, int nx,
                               const int2 *bwd, int nbwd, size_t lds_fwd, size_t lds_x, size_t lds_bwd, int tp,
@@ -1364,13 +1385,16 @@ static void launch_batch_mesh(const BatchMember *mem, int ik, const int2 *fwd, i
   if (tm) tm->after(7, st);
 }
 
-hipError_t launch_batch_recip(const BatchMember *mem, int precision, int ik, bool p4, const int2 *fwd, int nfwd,
+hipError_t launch_batch_recip(const BatchMember *mem, int precision, int ik, int p4, const int2 *fwd, int nfwd,
                               const int2 *x, int nx, const int2 *bwd, int nbwd, size_t lds_fwd, size_t lds_x,
                               size_t lds_bwd, int pass_threads, int x_threads, hipStream_t st, KernelTimer *tm) {
   if (pass_threads < 1 || pass_threads > kPassThreads || x_threads < 1 || x_threads > kPassThreads)
     return hipErrorInvalidValue;
-  const auto f = precision == 0 ? (p4 ? launch_batch_mesh<double, 4> : launch_batch_mesh<double, 0>)
-                                : (p4 ? launch_batch_mesh<float, 4> : launch_batch_mesh<float, 0>);
+  const auto f64 = p4 == 4 ? launch_batch_mesh<double, 4>
+                           : (p4 == 0 ? launch_batch_mesh<double, 0> : launch_batch_mesh<double, kAnyHalf>);
+  const auto f32 = p4 == 4 ? launch_batch_mesh<float, 4>
+                           : (p4 == 0 ? launch_batch_mesh<float, 0> : launch_batch_mesh<float, kAnyHalf>);
+  const auto f = precision == 0 ? f64 : f32;
   f(mem, ik, fwd, nfwd, x, nx, bwd, nbwd, lds_fwd, lds_x, lds_bwd, pass_threads, x_threads, st, tm);
   return hipGetLastError();
 }
@@ -1449,6 +1473,9 @@ hipError_t configure_kernels(size_t max_lds) {
       (const void *)k_recip_bwd<double, true, 4>,   (const void *)k_recip_bwd<float, true, 4>,
       (const void *)kb_recip_fwd<double, 0>,        (const void *)kb_recip_fwd<float, 0>,
       (const void *)kb_recip_fwd<double, 4>,        (const void *)kb_recip_fwd<float, 4>,
+      (const void *)kb_recip_fwd<double, kAnyHalf>, (const void *)kb_recip_fwd<float, kAnyHalf>,
+      (const void *)kb_recip_bwd<double, false, kAnyHalf>, (const void *)kb_recip_bwd<float, false, kAnyHalf>,
+      (const void *)kb_recip_bwd<double, true, kAnyHalf>,  (const void *)kb_recip_bwd<float, true, kAnyHalf>,
       (const void *)kb_recip_x<double>,             (const void *)kb_recip_x<float>,
       (const void *)kb_recip_bwd<double, false, 0>, (const void *)kb_recip_bwd<float, false, 0>,
       (const void *)kb_recip_bwd<double, true, 0>,  (const void *)kb_recip_bwd<float, true, 0>,

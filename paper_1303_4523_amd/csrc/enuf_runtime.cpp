@@ -329,8 +329,9 @@ void window8_rows(int fp32, int D, std::vector<long double> *coef) {
   if (D >= 1) t1[1] = 1.0L;
   for (int k = 0; k <= D; ++k) {
     const std::vector<long double> &t = k == 0 ? t0 : t1;
-    for (int i = 0; i < 16; ++i)
-      for (int m = 0; m <= D; ++m) mono[(size_t)i * (D + 1) + m] += c[(size_t)i * (D + 1) + k] * t[m];
+    for (int h = 0; h < 2; ++h)
+      for (int i = 8 * h; i < 8 * h + 4; ++i)  // (T_k has the powers of k's parity)
+        for (int m = k & 1; m <= k; m += 2) mono[(size_t)i * (D + 1) + m] += c[(size_t)i * (D + 1) + k] * t[m];
     if (k >= 1) {
       for (int m = 0; m <= D; ++m) t2[m] = (m > 0 ? 2.0L * t1[m - 1] : 0.0L) - t0[m];
       t0 = t1;
@@ -1760,7 +1761,7 @@ struct enuf_batch {
   int concurrent = 1;
   int use_graph = 1;
   int ik = -1;       // force mode of the members (all alike; -1 while empty)
-  bool p4 = false;   // mesh_win8 of every member
+  int p4 = 0;        // mesh_win8 of every member (4), of none (0) or of some (-1)
   std::vector<Member> members;
   int next_id = 0;
   // device copies of the member table and the work maps (rebuilt when the
@@ -1882,7 +1883,7 @@ int batch_rebuild(enuf_batch *b) {
   std::vector<int2> map[7];
   size_t lf = 0, lx = 0, lb = 0;
   int tp = b->tune.pass_threads, tx = b->tune.x_threads;  // enough threads for every member's FFT passes
-  bool p4 = true;
+  int n4 = 0;
   for (int k : order) {
     const BatchMember m = member_view(b->members[k], b->tune, 0);
     const int id = (int)mem.size();
@@ -1894,7 +1895,7 @@ int batch_rebuild(enuf_batch *b) {
                            bplanes, m.nblk};
     for (int s = 0; s < 7; ++s)
       for (int i = 0; i < counts[s]; ++i) map[s].push_back(make_int2(id, i));
-    p4 = p4 && mesh_win8(m.cfg.mesh);
+    n4 += mesh_win8(m.cfg.mesh) ? 1 : 0;
     lf = std::max(lf, m.cfg.lds_fwd);
     lx = std::max(lx, m.cfg.lds_x);
     lb = std::max(lb, m.cfg.lds_bwd);
@@ -1947,7 +1948,7 @@ int batch_rebuild(enuf_batch *b) {
   b->lds_fwd = lf;
   b->lds_x = lx;
   b->lds_bwd = lb;
-  b->p4 = p4;
+  b->p4 = n4 == (int)order.size() ? 4 : (n4 == 0 ? 0 : -1);
   b->pass_threads = tp;
   b->x_threads = tx;
   b->drop_graph();
