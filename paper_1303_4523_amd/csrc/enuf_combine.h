@@ -132,10 +132,10 @@ combine_body(int64_t N, gptr<const int> __restrict__ slot, gptr<const double4> _
     eg = block_sum(eg, s_dbl);
     er = block_sum_ll(er, s_ll);
     esl = block_sum_ll(esl, s_ll);
-    if (tid == 0) {
-      blk_eg[bid] = eg;
-      blk_er[2 * bid] = er;
-      blk_er[2 * bid + 1] = esl;
+    if (tid == 0) {  // (device scope: the launch's last work-group may read them)
+      __hip_atomic_store(blk_eg + bid, eg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(blk_er + 2 * bid, er, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(blk_er + 2 * bid + 1, esl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }

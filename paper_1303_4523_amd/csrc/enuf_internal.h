@@ -83,6 +83,7 @@ struct DevScalars {
   double sum_absq;
   double sum_q2;
   RealSplit split;      // work split of the real-space kernel for these charges
+  int done;             // combine work-groups that have left their energy partials (0 between launches)
 };
 
 // Mixed-radix factorisation of an FFT length, radices in {2, 3, 4, 5, 8}.
