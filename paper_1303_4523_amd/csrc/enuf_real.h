@@ -286,6 +286,8 @@ constexpr int kRealLanes = kWave / kRealU;
 constexpr int kRealCells = 9 * (kRealSegMax + 2);
 static_assert(kRealCells <= kWave && kRealOwn <= kRealThreads, "a lane per staged cell, a thread per charge");
 
+template <bool B> struct RealImage { static constexpr bool value = B; };
+
 struct RealShared {
   double4 pos[kRealStage];                // staged candidates (x, y, z, q)
   float4 rel[kRealStage];                 // FP32 position relative to the segment; grid slot in w
@@ -401,8 +403,10 @@ static __device__ __attribute__((noinline)) int real_redo(RealShared *sh, const 
 // The charges of segment [z0, z0 + zn) of column (cx, cy), those with place
 // first, first + 1, .. first + count - 1 (then first + step, ...) in the
 // segment's z-ordered list.  Staged cells are taken in the periodic image next
-// to the segment (grids of fewer than 3 cells per side, where a cell can be
-// its own neighbour, pass every candidate on to the FP64 test).
+// to the segment; on grids of fewer than 3 cells per side, where a cell can be its
+// own neighbour, the FP32 test takes the minimum image (1600 particles, all
+// charged, 2 cells per side: 119 us an evaluation when every candidate went on to
+// the FP64 test, 95 with it).
 __device__ __forceinline__ void
 real_segment(RealShared &sh, gptr<const int> __restrict__ ccnt, gptr<const double4> __restrict__ cgrid,
              gptr<const int> __restrict__ cidx, const CellParams &cp, double L, double rc2, const RealParams &rp,
@@ -453,7 +457,9 @@ real_segment(RealShared &sh, gptr<const int> __restrict__ ccnt, gptr<const doubl
     }
   }
   const double invL = 1.0 / L;
-  const float rc2f = n < 3 ? 3.0e38f : real_pretest_r2(rc2, L);
+  const float rc2f = real_pretest_r2(rc2, L);
+  const bool wrap = n < 3;
+  const float Lf = (float)L, invLf = 1.0f / Lf;
   // FP32 position of a charge of staged cell k
   auto relative = [&](const double4 &c, int k, int slot) {
     return make_float4((float)(c.x + sh.shift[k][0]), (float)(c.y + sh.shift[k][1]), (float)(c.z + sh.shift[k][2]),
@@ -566,20 +572,31 @@ real_segment(RealShared &sh, gptr<const int> __restrict__ ccnt, gptr<const doubl
 #pragma unroll
           for (int v = 0; v < kRealU; ++v) nl[v] = 0;
           {
+            auto scan = [&](auto image) {  // image: minimum image
 #pragma unroll 1
-            for (int h = s0; h < s1; h += kWave) {
-              const int ci = h + lane;
-              float4 cj = sh.rel[ci < s1 ? ci : s0];
-              if (ci >= s1) cj.x = __builtin_nanf("");
+              for (int h = s0; h < s1; h += kWave) {
+                const int ci = h + lane;
+                float4 cj = sh.rel[ci < s1 ? ci : s0];
+                if (ci >= s1) cj.x = __builtin_nanf("");
 #pragma unroll
-              for (int v = 0; v < kRealU; ++v) {
-                const float dx = cx4[v] - cj.x, dy = cy4[v] - cj.y, dz = cz4[v] - cj.z;
-                const bool take = dx * dx + dy * dy + dz * dz < rc2f;
-                const unsigned long long mk = __ballot(take);
-                if (take) sh.list[w][v][nl[v] + lanes_below(mk)] = (unsigned short)ci;
-                nl[v] += (int)__popcll(mk);
+                for (int v = 0; v < kRealU; ++v) {
+                  float dx = cx4[v] - cj.x, dy = cy4[v] - cj.y, dz = cz4[v] - cj.z;
+                  if constexpr (decltype(image)::value) {
+                    dx -= Lf * rintf(dx * invLf);
+                    dy -= Lf * rintf(dy * invLf);
+                    dz -= Lf * rintf(dz * invLf);
+                  }
+                  const bool take = dx * dx + dy * dy + dz * dz < rc2f;
+                  const unsigned long long mk = __ballot(take);
+                  if (take) sh.list[w][v][nl[v] + lanes_below(mk)] = (unsigned short)ci;
+                  nl[v] += (int)__popcll(mk);
+                }
               }
-            }
+            };
+            if (wrap)
+              scan(RealImage<true>());
+            else
+              scan(RealImage<false>());
             wave_sync();
             int most = nl[0], mine = nl[0];
 #pragma unroll
