@@ -32,7 +32,7 @@ struct DpdCharges {
   int *slot = nullptr;          // plan: slot map read by the combine kernel
   int *ccnt = nullptr;          // plan: charge cell grid
   double4 *cgrid = nullptr;
-  int *cidx = nullptr;
+  float4 *cpre = nullptr;
   CellParams cells{};
   unsigned long long *freal = nullptr, *ereal = nullptr;  // plan: real-space results (zeroed for charges
                                                           // that a full cell has no slot for)
@@ -51,7 +51,6 @@ struct DpdCharges {
 struct BatchMember {
   ComputeConfig cfg;
   ComputeBuffers buf;
-  int nq;                       // charged particles (static compaction)
   int nblk;                     // blocks of 256 particles (pre, combine)
   int pair_blocks;              // blocks of the pair kernel
   int real_blocks;              // blocks of the real-space kernel
@@ -98,7 +97,8 @@ hipError_t configure_pair_kernels(size_t lds_bytes);
 // Blocks of the pair kernel (one per column segment), a multiple of 8 (whole
 // rounds over the XCDs).
 int pair_blocks(const DpdParams &P);
-hipError_t launch_batch_real(const BatchMember *mem, const int2 *map, int nmap, int energies, hipStream_t st);
+// scan: that of every member, or kRealAny.
+hipError_t launch_batch_real(const BatchMember *mem, const int2 *map, int nmap, int scan, int energies, hipStream_t st);
 // pass_threads, x_threads: work-group sizes of the spread/gather passes and of
 // the x pass (at least fft_max_butterflies of every member).  p4: 4
 // (mesh_win8 of every member), 0 (of none) or -1 (of some).
@@ -125,7 +125,7 @@ hipError_t launch_dpd_pair(int64_t N, const DpdParams &P, uint64_t step, const d
 hipError_t launch_dpd_pair_real(const DpdParams &P, uint64_t step, const double *pos, const int *dcnt,
                                 const double4 *cpos, const double4 *cvel, const int *bond_start, const int *bond_to,
                                 double *fdpd, const ComputeConfig &cfg, const ComputeBuffers &b, int64_t nq_max,
-                                int energies, hipStream_t st, const unsigned long long *step_dev);
+                                int scan, int energies, hipStream_t st, const unsigned long long *step_dev);
 // The combine kernel of a DPD step fused with the next step's pre kernel
 // (no energy reduction: fa.energies must be 0, else hipErrorInvalidValue).
 hipError_t launch_combine_pre(const ComputeConfig &cfg, const ComputeBuffers &b, double *forces,

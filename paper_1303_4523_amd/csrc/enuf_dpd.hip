@@ -79,7 +79,7 @@ __device__ __forceinline__ void dpd_pre_scalars(const DpdCharges &ch, int64_t i)
     ch.sc->split.shares = ch.stat.split.shares;
     ch.sc->split.group = ch.stat.split.group;
     ch.sc->split.items = ch.stat.split.items;
-    ch.sc->split.per_charge = ch.stat.split.per_charge;
+    ch.sc->split.wave = ch.stat.split.wave;
   }
 }
 
@@ -149,7 +149,7 @@ dpd_pre_particle(int64_t i, int mode, const DpdParams &P, double *r, double *v, 
       const CellParams &cp = ch.cells;
       if (sl < cp.cap) {
         ch.cgrid[(size_t)c * cp.cap + sl] = make_double4(r[0], r[1], r[2], qi);
-        ch.cidx[(size_t)c * cp.cap + sl] = j;
+        ch.cpre[(size_t)c * cp.cap + sl] = make_float4((float)r[0], (float)r[1], (float)r[2], __int_as_float(j));
       } else {  // not in the grid: no real-space force
         atomicCAS(&ch.sc->status, 0, kEOverflow);
         for (int a = 0; a < 3; ++a) ch.freal[3 * (size_t)j + a] = 0ull;
@@ -641,7 +641,7 @@ struct RealArgs {
   const double4 *xq;
   const int *ccnt;
   const double4 *cgrid;
-  const int *cidx;
+  const float4 *cpre;
   CellParams cells;
   double L, alpha, rc2, lambda;
   DevScalars *sc;
@@ -649,6 +649,7 @@ struct RealArgs {
   int energies, blocks;
 };
 static_assert(kRealThreads == kPairThreads, "one launch");
+template <int SCAN>
 __global__ void __launch_bounds__(kPairThreads)
 k_dpd_pair_real(DpdParams P, uint64_t step, const unsigned long long *step_dev, const double *__restrict__ pos,
                 const int *__restrict__ dcnt, const double4 *__restrict__ cpos, const double4 *__restrict__ cvel,
@@ -660,7 +661,7 @@ k_dpd_pair_real(DpdParams P, uint64_t step, const unsigned long long *step_dev, 
     dpd_pair_body<kPairU, true>(P, step_dev ? (uint64_t)*step_dev : step, to_g(pos), to_g(dcnt), to_g(cpos),
                                 to_g(cvel), to_g(bond_start), to_g(bond_to), to_g(fdpd), b, npair);
   else
-    real_body(to_g(real.xq), to_g(real.ccnt), to_g(real.cgrid), to_g(real.cidx), real.cells, real.L, real.alpha,
+    real_body<SCAN>(to_g(real.xq), to_g(real.ccnt), to_g(real.cgrid), to_g(real.cpre), gptr<const int>(nullptr), real.cells, real.L, real.alpha,
               real.rc2, real.lambda, to_g(real.sc), to_g(real.freal), to_g(real.ereal), real.energies,
               *reinterpret_cast<RealShared *>(pair_real_smem), b - npair, real.blocks);
 }
@@ -828,9 +829,11 @@ constexpr size_t kBatchPairLdsBytes = (size_t)kBatchPairStage * (sizeof(double4)
 hipError_t configure_pair_kernels(size_t lds_bytes) {
   const int v = (int)(lds_bytes > kPairLdsBytes ? lds_bytes : kPairLdsBytes);
   hipError_t e = hipFuncSetAttribute((const void *)k_dpd_pair, hipFuncAttributeMaxDynamicSharedMemorySize, v);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute((const void *)k_dpd_pair_real, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            v > (int)sizeof(RealShared) ? v : (int)sizeof(RealShared));
+  const void *pr[] = {(const void *)k_dpd_pair_real<kRealSegment>, (const void *)k_dpd_pair_real<kRealWave>};
+  for (const void *f : pr)
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              v > (int)sizeof(RealShared) ? v : (int)sizeof(RealShared));
   const void *k[] = {(const void *)kb_dpd_pair<4>, (const void *)kb_dpd_pair<8>};
   for (const void *f : k)
     if (e == hipSuccess)
@@ -895,11 +898,11 @@ hipError_t launch_dpd_pair(int64_t N, const DpdParams &P, uint64_t step, const d
 hipError_t launch_dpd_pair_real(const DpdParams &P, uint64_t step, const double *pos, const int *dcnt,
                                 const double4 *cpos, const double4 *cvel, const int *bond_start, const int *bond_to,
                                 double *fdpd, const ComputeConfig &cfg, const ComputeBuffers &b, int64_t nq_max,
-                                int energies, hipStream_t st, const unsigned long long *step_dev) {
-  const RealArgs real = {b.xq, b.ccnt, b.cgrid, b.cidx, cfg.cells, cfg.L, cfg.alpha, cfg.r_cut * cfg.r_cut,
-                         cfg.lambda, b.sc, b.freal, b.ereal, energies, real_blocks(cfg.cells, nq_max, kRealDpdBlocks)};
+                                int scan, int energies, hipStream_t st, const unsigned long long *step_dev) {
+  const RealArgs real = {b.xq, b.ccnt, b.cgrid, b.cpre, cfg.cells, cfg.L, cfg.alpha, cfg.r_cut * cfg.r_cut,
+                         cfg.lambda, b.sc, b.freal, b.ereal, energies, real_blocks(cfg.cells, nq_max, kRealDpdBlocks, kRealDpdBlocks)};
   const size_t lds = pair_lds_bytes(P, true);
-  hipLaunchKernelGGL(k_dpd_pair_real, dim3(pair_blocks(P) + real.blocks), dim3(kPairThreads),
+  hipLaunchKernelGGL(scan == kRealWave ? k_dpd_pair_real<kRealWave> : k_dpd_pair_real<kRealSegment>, dim3(pair_blocks(P) + real.blocks), dim3(kPairThreads),
                      lds > sizeof(RealShared) ? lds : sizeof(RealShared), st, P, step, step_dev, pos, dcnt, cpos,
                      cvel, bond_start, bond_to, fdpd, real);
   return hipGetLastError();

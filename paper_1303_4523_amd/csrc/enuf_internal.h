@@ -28,24 +28,43 @@ constexpr int kBatchStage = 256;
 constexpr int kBatchXThreads = 128;
 constexpr int kMaxParts = 8;       // most work-groups per plane in the spread and gather passes
 
-// Real-space work split.  A block takes a segment of `seg` cells of a column,
-// or, where cells are full or the grid has few cells, one of the `shares` of a
-// cell's charges; at most kRealOwn charges at a time.  A single evaluation asks
-// for about kRealTargetBlocks blocks; a DPD step, where the pair kernel and the
-// mesh passes share the device, for kRealDpdBlocks (642 against 678 us per 11
-// steps at N = 3333, the same at N = 24000); batches, which fill the device,
-// for none.  Larger targets for one evaluation (1024, 2048) gained on 27 full
-// cells (98 -> 88 us) and lost on sparse ones (14.9 -> 17.7 us).
+// Real-space work split.  Two scans:
+//  * segments: a block takes a segment of `seg` cells of a column, or, where
+//    cells are full or the grid has few cells, one of the `shares` of a cell's
+//    charges, at most kRealOwn at a time, and stages their candidates once;
+//  * `wave`: a wavefront per charge reads its candidates itself.
+// `blocks` is the number of blocks to ask for: kRealTargetBlocks for a single
+// evaluation; kRealDpdBlocks for a DPD step, where the pair kernel and the mesh
+// passes share the device (642 against 678 us per 11 steps at N = 3333, the same
+// at N = 24000); none for batches, which fill the device.
+// Staging pays where a cell's charges share it: 24000 charges, 6 per cell, 36 us
+// a launch against 52 by wavefronts, 47 per cell 121 against 137.  With fewer
+// than 2 per cell the 27 cells hold less than a block's lanes (24000 charges on
+// 77^3 cells 37 us against 165, on 24^3 cells, 1.7 per cell, 47 and 48).
+// On 3 or 4 cells per side a cell is cut into many shares, and each stages the
+// whole neighbourhood again (92 charges per cell on 3 cells per side: 42 us
+// against 63; 156 on 4: 135 against 171), so there the wavefronts take over
+// where `wave_blocks`, the blocks that the device has to spare, is 5 per cell or
+// more; from 5 cells per side on the two are alike (64 per cell: 61 and 81 us
+// alone, 125 and 132 beside the mesh passes; 96 per cell: 184 and 175).  On 2
+// cells per side 8 of the 27 places have a cell, so that a wavefront's lanes are
+// two thirds idle: only up to 16 charges per cell (12.5 per cell: 13.1 us
+// against 14.6; 250: 58.8 and 58.7).
+constexpr int kRealThreads = 256;
 constexpr int kRealOwn = 64;
 constexpr int kRealSegMax = 4;
 constexpr int kRealTargetBlocks = 512, kRealDpdBlocks = 216;
-constexpr int kRealFill = 336;   // staged candidates a segment may expect (of a stage of 384)
+constexpr int kRealStage = 384;  // candidates staged at a time
+constexpr int kRealFill = 336;   // staged candidates a segment may expect
+constexpr int kRealWaveBlocks = 2048;  // most blocks of the wavefront-per-charge scan
+enum : int { kRealAny = -1, kRealSegment = 0, kRealWave = 1 };  // scans of the real-space kernels
 struct RealSplit {
   int seg, nseg, shares, group;
   int items;        // blocks' worth of work
-  int per_charge;   // far fewer charges than cells: an item per charge
+  int wave;         // a wavefront per charge instead
 };
-__host__ __device__ inline RealSplit real_split(int nq, int n, int blocks) {
+// (a wave split stays one for fewer charges)
+__host__ __device__ inline RealSplit real_split(int nq, int n, int blocks, int wave_blocks) {
   RealSplit s;
   const int n2 = n * n, n3 = n2 * n;
   const int mean = nq / n3 + 1;  // charges per cell, rounded up
@@ -68,8 +87,8 @@ __host__ __device__ inline RealSplit real_split(int nq, int n, int blocks) {
     s.group = ((full + s.shares - 1) / s.shares + 3) / 4 * 4;
     s.group = s.group < kRealOwn ? s.group : kRealOwn;
   }
-  s.per_charge = nq < n3 / 8;
-  s.items = s.per_charge ? nq : n2 * s.nseg * s.shares;
+  s.wave = nq < 2 * n3 || (wave_blocks >= 5 * n3 && (n >= 3 || nq < 16 * n3));
+  s.items = s.wave ? (nq + kRealThreads / kWave - 1) / (kRealThreads / kWave) : n2 * s.nseg * s.shares;
   return s;
 }
 
@@ -199,7 +218,9 @@ struct ComputeBuffers {
   // real-space cell grid
   int *ccnt;             // [2 ncell^3] two sets: a DPD step bins into one while the other is cleared
   double4 *cgrid;        // [ncell^3 * cap] (x, y, z, q) per cell slot
-  int *cidx;             // [ncell^3 * cap] compact index per cell slot
+  float4 *cpre;          // [ncell^3 * cap] FP32 (x, y, z) and the compact index (bits in w) per cell
+                         // slot: what the wavefront-per-charge scan reads
+  int *cidx;             // without cpre: the compact index alone
   unsigned long long *freal;  // [N * 3] fixed-point real-space force per compact slot
   unsigned long long *ereal; // [2 N] fixed-point (E_real whole, E_slater) of the pairs (j, k > j), per compact slot j
   long long *blk_er;         // [2 nblk] per-block sums of ereal over the particles of the block
@@ -277,11 +298,17 @@ inline double combine_fscale(const ComputeConfig &cfg) {
 hipError_t launch_prep(const ComputeConfig &cfg, const ComputeBuffers &b, const double *pos,
                        const double *q, hipStream_t st, KernelTimer *tm);
 // Blocks of the real-space kernel for up to nq_max charges.
-int real_blocks(const CellParams &cp, int64_t nq_max, int blocks);
+int real_blocks(const CellParams &cp, int64_t nq_max, int blocks, int wave_blocks);
 // energies: also leave the charges' pair energies (a step whose energies no one
 // reads skips them).
-hipError_t launch_real(const ComputeConfig &cfg, const ComputeBuffers &b, int64_t nq_max, int energies,
+// scan: the scan of the split left in the scalars, or kRealAny.
+hipError_t launch_real(const ComputeConfig &cfg, const ComputeBuffers &b, int64_t nq_max, int scan, int energies,
                        hipStream_t st, KernelTimer *tm);
+// The scan of an evaluation of up to N charges (one that real_split takes for N
+// it takes for fewer).
+inline int eval_scan(const ComputeConfig &cfg) {
+  return real_split((int)cfg.N, cfg.cells.ncell, kRealTargetBlocks, kRealTargetBlocks).wave ? kRealWave : kRealAny;
+}
 // x_threads: work-group size of the x pass (at least fft_max_butterflies of
 // the mesh, at most kPassThreads; others are raised or clamped to fit).
 hipError_t launch_recip(const ComputeConfig &cfg, const ComputeBuffers &b, int64_t nq_max, hipStream_t st,

@@ -93,7 +93,7 @@ __device__ inline void prep_scalars(int nblk, const int *__restrict__ blk_cnt, c
     sc->sum_q = a;
     sc->sum_absq = b;
     sc->sum_q2 = c;
-    sc->split = real_split(nq, ncell, kRealTargetBlocks);
+    sc->split = real_split(nq, ncell, kRealTargetBlocks, kRealTargetBlocks);
     // Mesh values are bounded by sum |q| (the window is <= 1): choose the
     // largest power of two keeping sum|q| * scale below 2^61.
     int e;
@@ -108,7 +108,7 @@ __global__ void __launch_bounds__(kPrepThreads)
 k_prep_compact(int64_t N, const double *__restrict__ pos, const double *__restrict__ q,
                double L, CellParams cp, const int *__restrict__ blk_cnt, int nblk,
                const double *__restrict__ blk_sums, double4 *xq, int *idx, int *slot, int *ccnt, double4 *cgrid,
-               int *cidx, int *xcnt, int *xslot, int M, double m_over_l, int xcap,
+               float4 *cpre, int *cidx, int *xcnt, int *xslot, int M, double m_over_l, int xcap,
                unsigned long long *freal, unsigned long long *ereal, DevScalars *sc) {
   __shared__ int s_int[kPrepThreads / kWave];
   __shared__ int s_wcnt[kPrepThreads / kWave];
@@ -153,7 +153,10 @@ k_prep_compact(int64_t N, const double *__restrict__ pos, const double *__restri
       const int s = atomicAdd(&ccnt[cell], 1);
       if (s < cp.cap) {
         cgrid[(size_t)cell * cp.cap + s] = make_double4(x, y, z, qi);
-        cidx[(size_t)cell * cp.cap + s] = j;
+        if (cpre)
+          cpre[(size_t)cell * cp.cap + s] = make_float4((float)x, (float)y, (float)z, __int_as_float(j));
+        else
+          cidx[(size_t)cell * cp.cap + s] = j;
       } else {  // not in the grid: no real-space force
         set_status(sc, kEOverflow);
         for (int a = 0; a < 3; ++a) freal[3 * (size_t)j + a] = 0ull;
@@ -174,13 +177,13 @@ k_prep_compact(int64_t N, const double *__restrict__ pos, const double *__restri
   }
 }
 
+template <int SCAN, bool COPY>
 __global__ void __launch_bounds__(kRealThreads, 4)
 k_real(const double4 *__restrict__ xq, const int *__restrict__ ccnt, const double4 *__restrict__ cgrid,
-       const int *__restrict__ cidx,
-       CellParams cp, double L, double alpha, double rc2, double lam, DevScalars *sc, unsigned long long *freal,
+       const float4 *__restrict__ cpre, const int *__restrict__ cidx, CellParams cp, double L, double alpha, double rc2, double lam, DevScalars *sc, unsigned long long *freal,
        unsigned long long *ereal, int energies) {
   __shared__ RealShared sh;
-  real_body(to_g(xq), to_g(ccnt), to_g(cgrid), to_g(cidx), cp, L, alpha, rc2, lam, to_g(sc), to_g(freal), to_g(ereal),
+  real_body<SCAN, COPY>(to_g(xq), to_g(ccnt), to_g(cgrid), to_g(cpre), to_g(cidx), cp, L, alpha, rc2, lam, to_g(sc), to_g(freal), to_g(ereal),
             energies, sh, blockIdx.x, gridDim.x);
 }
 
@@ -1281,12 +1284,13 @@ k_combine(int64_t N, const int *__restrict__ slot, const double4 *__restrict__ x
 // Batched kernels: one launch covers every member of a batch; block b works
 // on block map[b].y of member map[b].x with that member's geometry and buffers.
 // ---------------------------------------------------------------------------
+template <int SCAN>
 __global__ void __launch_bounds__(kRealThreads, 4)
 kb_real(const BatchMember *__restrict__ mem, const int2 *__restrict__ map, int energies) {
   const int2 w = map[blockIdx.x];
   const BatchMember &m = mem[w.x];
   __shared__ RealShared sh;
-  real_body(to_g(m.buf.xq), to_g(m.buf.ccnt), to_g(m.buf.cgrid), to_g(m.buf.cidx), m.cfg.cells, m.cfg.L, m.cfg.alpha,
+  real_body<SCAN>(to_g(m.buf.xq), to_g(m.buf.ccnt), to_g(m.buf.cgrid), to_g(m.buf.cpre), gptr<const int>(nullptr), m.cfg.cells, m.cfg.L, m.cfg.alpha,
             m.cfg.r_cut * m.cfg.r_cut, m.cfg.lambda, to_g(m.buf.sc), to_g(m.buf.freal), to_g(m.buf.ereal), energies, sh,
             w.y, m.real_blocks);
 }
@@ -1385,8 +1389,9 @@ kb_finish(const BatchMember *__restrict__ mem, int mode) {
               nullptr, m.e5, mode == 0 ? m.step : nullptr);
 }
 
-hipError_t launch_batch_real(const BatchMember *mem, const int2 *map, int nmap, int energies, hipStream_t st) {
-  if (nmap > 0) hipLaunchKernelGGL(kb_real, dim3(nmap), dim3(kRealThreads), 0, st, mem, map, energies);
+hipError_t launch_batch_real(const BatchMember *mem, const int2 *map, int nmap, int scan, int energies, hipStream_t st) {
+  const auto k = scan == kRealSegment ? kb_real<kRealSegment> : (scan == kRealWave ? kb_real<kRealWave> : kb_real<kRealAny>);
+  if (nmap > 0) hipLaunchKernelGGL(k, dim3(nmap), dim3(kRealThreads), 0, st, mem, map, energies);
   return hipGetLastError();
 }
 
@@ -1554,25 +1559,29 @@ hipError_t launch_prep(const ComputeConfig &cfg, const ComputeBuffers &b, const 
   if (tm) tm->before(3, st);
   hipLaunchKernelGGL(k_prep_compact, dim3(nblk), dim3(kPrepThreads), 0, st, cfg.N, pos, q, cfg.L, cfg.cells,
                      (const int *)b.blk_cnt, nblk, (const double *)b.blk_sums, b.xq, b.idx, b.slot, b.ccnt,
-                     b.cgrid, b.cidx, b.xcnt, b.xslot, cfg.mesh.M, cfg.mesh.m_over_l, cfg.mesh.xcap, b.freal, b.ereal,
+                     b.cgrid, b.cpre, b.cidx, b.xcnt, b.xslot, cfg.mesh.M, cfg.mesh.m_over_l, cfg.mesh.xcap, b.freal, b.ereal,
                      b.sc);
   if (tm) tm->after(3, st);
   return hipGetLastError();
 }
 
-int real_blocks(const CellParams &cp, int64_t nq_max, int blocks) {
-  int64_t items = real_split((int)nq_max, cp.ncell, blocks).items;
+int real_blocks(const CellParams &cp, int64_t nq_max, int blocks, int wave_blocks) {
+  const RealSplit s = real_split((int)nq_max, cp.ncell, blocks, wave_blocks);
   // fewer charges than the bound may be split otherwise; the blocks loop over
   // their items, so the bound's count (at least the fill target) serves any
-  items = items > blocks ? items : blocks;
-  return (int)(items < 1 ? 1 : (items < 65536 ? items : 65536));
+  const int items = s.wave ? (s.items < kRealWaveBlocks ? s.items : kRealWaveBlocks)
+                           : (s.items < 65536 ? s.items : 65536);
+  return items > blocks ? items : (blocks > 1 ? blocks : 1);
 }
 
-hipError_t launch_real(const ComputeConfig &cfg, const ComputeBuffers &b, int64_t nq_max, int energies,
+hipError_t launch_real(const ComputeConfig &cfg, const ComputeBuffers &b, int64_t nq_max, int scan, int energies,
                        hipStream_t st, KernelTimer *tm) {
+  const auto k = !b.cpre ? k_real<kRealAny, false>
+                         : (scan == kRealSegment ? k_real<kRealSegment, true>
+                                                 : (scan == kRealWave ? k_real<kRealWave, true> : k_real<kRealAny, true>));
   if (tm) tm->before(4, st);
-  hipLaunchKernelGGL(k_real, dim3(real_blocks(cfg.cells, nq_max, kRealTargetBlocks)), dim3(kRealThreads), 0, st,
-                     (const double4 *)b.xq, (const int *)b.ccnt, (const double4 *)b.cgrid, (const int *)b.cidx,
+  hipLaunchKernelGGL(k, dim3(real_blocks(cfg.cells, nq_max, kRealTargetBlocks, kRealTargetBlocks)), dim3(kRealThreads), 0, st,
+                     (const double4 *)b.xq, (const int *)b.ccnt, (const double4 *)b.cgrid, (const float4 *)b.cpre, (const int *)b.cidx,
                      cfg.cells, cfg.L, cfg.alpha, cfg.r_cut * cfg.r_cut, cfg.lambda, b.sc, b.freal, b.ereal,
                      energies);
   if (tm) tm->after(4, st);
@@ -1623,7 +1632,7 @@ hipError_t launch_compute(const ComputeConfig &cfg, const ComputeBuffers &b, con
                           const double *q, double *forces, double *energy_total, double *energy5,
                           hipStream_t st, KernelTimer *tm) {
   hipError_t e = launch_prep(cfg, b, pos, q, st, tm);
-  if (e == hipSuccess) e = launch_real(cfg, b, cfg.N, 1, st, tm);
+  if (e == hipSuccess) e = launch_real(cfg, b, cfg.N, eval_scan(cfg), 1, st, tm);
   if (e == hipSuccess) e = launch_recip(cfg, b, cfg.N, st, tm);
   if (e == hipSuccess) e = launch_combine(cfg, b, forces, energy_total, energy5, FinishArgs(), st, tm);
   return e;

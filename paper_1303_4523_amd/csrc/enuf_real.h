@@ -278,9 +278,7 @@ __device__ inline bool cell_offset_valid(int o, int n) {
 // order does not matter.  (A wavefront per charge paid the four dependent
 // loads of cell counts, candidates and queued pairs for every charge and used
 // 24 of 64 lanes of an evaluation at 8 charges per cell.)
-constexpr int kRealThreads = 256;
 constexpr int kRealWaves = kRealThreads / kWave;
-constexpr int kRealStage = 384;  // candidates staged at a time
 constexpr int kRealU = 4;        // charges per unit of work
 constexpr int kRealLanes = kWave / kRealU;
 constexpr int kRealCells = 9 * (kRealSegMax + 2);
@@ -298,6 +296,7 @@ struct RealShared {
   int off[kRealCells + 1], gbase[kRealCells];  // first staged index and grid slot of each staged cell
   double shift[kRealCells][3];            // to the image next to the segment, relative to its first cell
   unsigned short list[kRealWaves][kRealU][kRealStage];  // candidates that passed, per charge of the unit
+                                                        // (wavefront per charge: its queue)
   unsigned char cellof[kRealStage];       // staged cell of each candidate
   ushort2 redo[kRealThreads];             // pairs (candidate, charge) for real_redo, of the block
   ushort2 spare[kRealWaves][kWave];       // and of a wavefront when there is no room
@@ -377,6 +376,18 @@ __device__ __forceinline__ double real_factor(double r, double a, double lam) {
 // the pairs in LDS and calling once a window keeps the call's registers out of
 // the loops (called in the loop: 411).
 constexpr double kRealSlack = 3.552713678800501e-15;  // 2^-48
+// The rounded force terms of a pair; false where real_redo has to form them.
+__device__ __forceinline__ bool real_rounds(double gf, double dx, double dy, double dz, double qq, double ir,
+                                            double *kx, double *ky, double *kz) {
+#pragma clang fp contract(off)
+  double mx, my, mz;
+  *kx = real_round(gf * dx, &mx);
+  *ky = real_round(gf * dy, &my);
+  *kz = real_round(gf * dz, &mz);
+  const double slack = fabs(qq) * (kRealSlack * kRealFxScale) * (ir * ir * ir);
+  return fma(slack, fabs(dx), mx) < 0.5 && fma(slack, fabs(dy), my) < 0.5 && fma(slack, fabs(dz), mz) < 0.5 &&
+         fabs(gf) * kRealFxScale < kRealSmall * ir;
+}
 static __device__ __attribute__((noinline)) int real_redo(RealShared *sh, const ushort2 *pairs, int n, double L, double alpha,
                                                    double lam) {
 #pragma clang fp contract(off)
@@ -400,6 +411,12 @@ static __device__ __attribute__((noinline)) int real_redo(RealShared *sh, const 
   return err;
 }
 
+// The compact index of a cell slot: in its FP32 copy, or alone (no COPY).
+template <bool COPY>
+__device__ __forceinline__ int real_index(gptr<const float4> cpre, gptr<const int> cidx, int slot) {
+  return COPY ? ((gptr<const int>)(cpre + slot))[3] : cidx[slot];
+}
+
 // The charges of segment [z0, z0 + zn) of column (cx, cy), those with place
 // first, first + 1, .. first + count - 1 (then first + step, ...) in the
 // segment's z-ordered list.  Staged cells are taken in the periodic image next
@@ -407,13 +424,18 @@ static __device__ __attribute__((noinline)) int real_redo(RealShared *sh, const 
 // own neighbour, the FP32 test takes the minimum image (1600 particles, all
 // charged, 2 cells per side: 119 us an evaluation when every candidate went on to
 // the FP64 test, 95 with it).
+template <bool COPY>
 __device__ __forceinline__ void
 real_segment(RealShared &sh, gptr<const int> __restrict__ ccnt, gptr<const double4> __restrict__ cgrid,
-             gptr<const int> __restrict__ cidx, const CellParams &cp, double L, double rc2, const RealParams &rp,
+             gptr<const float4> __restrict__ cpre, gptr<const int> __restrict__ cidx, const CellParams &cp, double L, double rc2, const RealParams &rp,
              gptr<DevScalars> sc, gptr<unsigned long long> freal, gptr<unsigned long long> ereal, int energies,
              int cx, int cy, int z0, int zn, int first, int step, int count) {
-  // (the wavefront's index is stated uniform, so that all that follows from it stays scalar)
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  // (the wavefront's index is stated uniform, so that all that follows from it stays scalar;
+  // the thread's index is opaque, so that what follows from it is formed again for
+  // each item instead of being held, and then spilled, across them)
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & (kWave - 1), w = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int n = cp.ncell, cap = cp.cap;
   // the staged cells, one per lane, in every wavefront: counts and prefix sums
   const int ncells = 9 * (zn + 2);
@@ -501,7 +523,7 @@ real_segment(RealShared &sh, gptr<const int> __restrict__ ccnt, gptr<const doubl
           }
           so = sh.gbase[ko] + b;
           co = gload(cgrid + so);
-          jo = cidx[so];
+          jo = real_index<COPY>(cpre, cidx, so);
         }
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
@@ -626,12 +648,8 @@ real_segment(RealShared &sh, gptr<const int> __restrict__ ccnt, gptr<const doubl
                   } else {
                     const double qq = pi.w * pj.w;
                     const double gf = qq * f;
-                    double mx, my, mz;
-                    const double kx = real_round(gf * dx, &mx), ky = real_round(gf * dy, &my),
-                                 kz = real_round(gf * dz, &mz);
-                    const double slack = fabs(qq) * (kRealSlack * kRealFxScale) * (ir * ir * ir);
-                    redo = !(fma(slack, fabs(dx), mx) < 0.5 && fma(slack, fabs(dy), my) < 0.5 &&
-                             fma(slack, fabs(dz), mz) < 0.5 && fabs(gf) * kRealFxScale < kRealSmall * ir);
+                    double kx, ky, kz;
+                    redo = !real_rounds(gf, dx, dy, dz, qq, ir, &kx, &ky, &kz);
                     if (!redo) {
                       fx += kx;
                       fy += ky;
@@ -731,35 +749,217 @@ real_segment(RealShared &sh, gptr<const int> __restrict__ ccnt, gptr<const doubl
   if (err) set_status(sc, err);
 }
 
-// Block bid of nbid takes the items of the charges' split in turn.
+// A wavefront per charge j: lanes 0..53 take one of the 27 neighbour cells and
+// every other slot in it, test each candidate in FP32 (the slot's FP32 copy, with
+// the margin of the pre-test; a call without copies rounds the position itself) and append those that pass to the
+// wavefront's queue in LDS; the wavefront takes the queued candidates 64 at a
+// time.  The pairs, their terms and so the charge's sums are those of
+// real_segment.  No barrier, no staging: one charge costs a few dependent loads
+// and the scan of its candidates, and every charge has its wavefront at once.
+// Bound by the latency of those loads where charges are few, by the scan where
+// they are dense (the choice of the scan, with both sides' times: real_split).
+// The sums stay in registers to the charge's end: added to LDS at every flush
+// they cost 42 -> 48 us (92 charges per cell, 3 cells per side).
+constexpr int kRealScan = 2;                        // candidates per lane and pass
+constexpr int kRealQueue = (kRealScan + 1) * kWave;  // queued candidates per wavefront
+constexpr int kRealLeft = kRealStage / kRealWaves;   // pairs kept for real_redo per wavefront
+static_assert(2 * kRealQueue * sizeof(int) <= kRealU * kRealStage * sizeof(unsigned short), "the queue takes the list's LDS");
+static_assert(kRealLeft >= kWave && kRealOwn >= kRealWaves, "pairs and charge of a wavefront for real_redo");
+template <bool COPY>
+__device__ __forceinline__ void
+real_charges(RealShared &sh, gptr<const double4> __restrict__ xq, gptr<const int> __restrict__ ccnt,
+             gptr<const double4> __restrict__ cgrid, gptr<const float4> __restrict__ cpre,
+             gptr<const int> __restrict__ cidx, const CellParams &cp, double L, double rc2, const RealParams &rp,
+             gptr<DevScalars> sc, gptr<unsigned long long> freal,
+             gptr<unsigned long long> ereal, int energies, int bid, int nbid) {
+  // (opaque, so that nothing of this scan is computed ahead of real_segment and
+  // held in its registers, nor the reverse)
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & (kWave - 1), w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  int *const qs = reinterpret_cast<int *>(&sh.list[w][0][0]);  // grid slot of each queued candidate
+  int *const qk = qs + kRealQueue;                             // and compact index
+  double4 *const left = sh.pos + w * kRealLeft;
+  const int nq = sc->nq, n = cp.ncell, cap = cp.cap;
+  const double invL = 1.0 / L;
+  const float Lf = (float)L, invLf = 1.0f / Lf, rc2f = real_pretest_r2(rc2, L);
+  auto wave_sync = []() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  int err = 0;
+  for (int j = bid * kRealWaves + w; j < nq; j += nbid * kRealWaves) {
+    const double4 pi = gload(xq + j);
+    const float xf = (float)pi.x, yf = (float)pi.y, zf = (float)pi.z;
+    const int cell = cell_of(pi.x, pi.y, pi.z, cp);
+    int cnt = 0, base = 0, s = lane / 27;
+    if (lane < 54) {
+      const int o = lane % 27, ox = o / 9 - 1, oy = (o / 3) % 3 - 1, oz = o % 3 - 1;
+      if (cell_offset_valid(ox, n) && cell_offset_valid(oy, n) && cell_offset_valid(oz, n)) {
+        const int cx = cell / (n * n), cy = (cell / n) % n, cz = cell % n;
+        const int c = (wrap_once(cx + ox, n) * n + wrap_once(cy + oy, n)) * n + wrap_once(cz + oz, n);
+        cnt = ccnt[c];
+        cnt = cnt < cap ? cnt : cap;
+        base = c * cap;
+      }
+    }
+    unsigned long long fx = 0, fy = 0, fz = 0, eu = 0, es = 0;
+    int qn = 0, nl = 0;  // queued candidates, pairs left to real_redo
+    auto redo_left = [&]() {
+      if (lane == 0) sh.own[w] = pi;
+      if (lane < 3) sh.acc[w][lane] = 0ull;
+      if (lane < nl) sh.spare[w][lane] = make_ushort2((unsigned short)(w * kRealLeft + lane), (unsigned short)w);
+      wave_sync();
+      const int e = real_redo(&sh, sh.spare[w], nl, L, rp.a, rp.lam);
+      err = e ? e : err;
+      wave_sync();
+      if (lane == 0) {
+        fx += sh.acc[w][0];
+        fy += sh.acc[w][1];
+        fz += sh.acc[w][2];
+      }
+      wave_sync();
+      nl = 0;
+    };
+    for (bool more = true; more;) {
+      // kRealScan loads a lane before the first is tested
+      bool live[kRealScan];
+      float4 cc[kRealScan];
+#pragma unroll
+      for (int u = 0; u < kRealScan; ++u) {
+        live[u] = s + 2 * u < cnt;
+        cc[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (live[u]) {
+          const int at = base + s + 2 * u;
+          if constexpr (COPY) {
+            cc[u] = gload(cpre + at);
+          } else {
+            const double4 c = gload(cgrid + at);
+            cc[u] = make_float4((float)c.x, (float)c.y, (float)c.z, __int_as_float(cidx[at]));
+          }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kRealScan; ++u) {
+        float dx = xf - cc[u].x, dy = yf - cc[u].y, dz = zf - cc[u].z;
+        dx -= Lf * rintf(dx * invLf);
+        dy -= Lf * rintf(dy * invLf);
+        dz -= Lf * rintf(dz * invLf);
+        const int k = __float_as_int(cc[u].w);
+        const bool take = live[u] && k != j && dx * dx + dy * dy + dz * dz < rc2f;
+        const unsigned long long m = __ballot(take);
+        if (take) {
+          const int at = qn + lanes_below(m);
+          qs[at] = base + s + 2 * u;
+          qk[at] = k;
+        }
+        qn += (int)__popcll(m);
+      }
+      s += 2 * kRealScan;
+      more = __ballot(s < cnt) != 0ull;
+      if (more && qn <= kRealQueue - kRealScan * kWave) continue;
+      wave_sync();
+      double sx = 0.0, sy = 0.0, sz = 0.0, su = 0.0, ss = 0.0;
+#pragma unroll 1
+      for (int e = lane; e - lane < qn; e += kWave) {
+        // minimum image and r^2 with their fused multiply-adds written out (no
+        // contraction left to the compiler, as in real_pair)
+#pragma clang fp contract(off)
+        bool redo = false;
+        double4 pj;
+        if (e < qn) {
+          const int k = qk[e];
+          pj = gload(cgrid + qs[e]);
+          double dx = pi.x - pj.x, dy = pi.y - pj.y, dz = pi.z - pj.z;
+          dx = fma(-L, rint(dx * invL), dx);
+          dy = fma(-L, rint(dy * invL), dy);
+          dz = fma(-L, rint(dz * invL), dz);
+          const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
+          double u, us, f, ir;
+          if (!(r2 < rc2)) {  // inside the FP32 margin only
+          } else if (!real_pair(rp, r2, &u, &us, &f, &ir)) {
+            err = kECoincident;
+          } else {
+            const double qq = pi.w * pj.w, gf = qq * f;
+            double kx, ky, kz;
+            redo = !real_rounds(gf, dx, dy, dz, qq, ir, &kx, &ky, &kz);
+            if (!redo) {
+              sx += kx;
+              sy += ky;
+              sz += kz;
+            }
+            if (energies && k > j) {
+              if (__builtin_expect(fmax(fabs(qq * u), fabs(qq * us)) * kRealFxScale < kRealSmall, 1)) {
+                real_add(su, qq * u);
+                real_add(ss, qq * us);
+              } else {
+                eu += (unsigned long long)to_fixed(qq * u, kRealFxScale);
+                es += (unsigned long long)to_fixed(qq * us, kRealFxScale);
+              }
+            }
+          }
+        }
+        const unsigned long long m = __ballot(redo);
+        if (m) {
+          if (nl + (int)__popcll(m) > kWave) redo_left();
+          if (redo) left[nl + lanes_below(m)] = pj;
+          nl += (int)__popcll(m);
+        }
+      }
+      fx += real_sum(sx);
+      fy += real_sum(sy);
+      fz += real_sum(sz);
+      if (energies) {
+        eu += real_sum(su);
+        es += real_sum(ss);
+      }
+      wave_sync();
+      qn = 0;
+    }
+    if (nl) redo_left();
+    fx = (unsigned long long)wave_sum_ll((long long)fx);
+    fy = (unsigned long long)wave_sum_ll((long long)fy);
+    fz = (unsigned long long)wave_sum_ll((long long)fz);
+    if (energies) {
+      eu = (unsigned long long)wave_sum_ll((long long)eu);
+      es = (unsigned long long)wave_sum_ll((long long)es);
+    }
+    if (lane == 0) {
+      freal[3 * (size_t)j] = fx;
+      freal[3 * (size_t)j + 1] = fy;
+      freal[3 * (size_t)j + 2] = fz;
+      if (energies) {
+        ereal[2 * (size_t)j] = eu;
+        ereal[2 * (size_t)j + 1] = es;
+      }
+    }
+  }
+  if (err) set_status(sc, err);
+}
+
+// Block bid of nbid takes the items of the charges' split in turn.  SCAN: the
+// scan of these charges where the host knows it (each alone takes fewer
+// registers), else kRealAny.
+template <int SCAN, bool COPY = true>
 __device__ __forceinline__ void
 real_body(gptr<const double4> __restrict__ xq, gptr<const int> __restrict__ ccnt,
-          gptr<const double4> __restrict__ cgrid, gptr<const int> __restrict__ cidx, const CellParams &cp, double L,
-          double alpha, double rc2, double lam, gptr<DevScalars> sc, gptr<unsigned long long> freal,
+          gptr<const double4> __restrict__ cgrid, gptr<const float4> __restrict__ cpre,
+          gptr<const int> __restrict__ cidx, const CellParams &cp, double L, double alpha, double rc2, double lam, gptr<DevScalars> sc, gptr<unsigned long long> freal,
           gptr<unsigned long long> ereal, int energies, RealShared &sh, int bid, int nbid) {
   const RealParams rp = real_params(alpha, rc2, lam);
   const int n = cp.ncell;
+  if (SCAN == kRealWave || (SCAN == kRealAny && sc->split.wave)) {
+    real_charges<COPY>(sh, xq, ccnt, cgrid, cpre, cidx, cp, L, rc2, rp, sc, freal, ereal, energies, bid, nbid);
+    return;
+  }
   const RealSplit sp = {sc->split.seg,   sc->split.nseg,  sc->split.shares,
-                        sc->split.group, sc->split.items, sc->split.per_charge};
+                        sc->split.group, sc->split.items, 0};
   for (int item = bid; item < sp.items; item += nbid) {
-    int cx, cy, z0, zn = 1, share = 0;
-    if (sp.per_charge) {
-      // far more cells than charges: the items are the charges, and the one in
-      // its cell's first slot takes the cell
-      const double4 c = gload(xq + item);
-      const int cell = cell_of(c.x, c.y, c.z, cp);
-      if (cidx[(size_t)cell * cp.cap] != item) continue;
-      cx = cell / (n * n);
-      cy = (cell / n) % n;
-      z0 = cell % n;
-    } else {
-      int seg, col;
-      share = divmod(divmod(item, sp.nseg, &seg), n * n, &col);
-      cx = divmod(col, n, &cy);
-      z0 = seg * sp.seg;
-      zn = (n - z0) < sp.seg ? (n - z0) : sp.seg;
-    }
-    real_segment(sh, ccnt, cgrid, cidx, cp, L, rc2, rp, sc, freal, ereal, energies, cx, cy, z0, zn,
+    int seg, col, cy;
+    const int share = divmod(divmod(item, sp.nseg, &seg), n * n, &col);
+    const int cx = divmod(col, n, &cy), z0 = seg * sp.seg, zn = (n - z0) < sp.seg ? (n - z0) : sp.seg;
+    real_segment<COPY>(sh, ccnt, cgrid, cpre, cidx, cp, L, rc2, rp, sc, freal, ereal, energies, cx, cy, z0, zn,
                  share * sp.group, sp.shares * sp.group, sp.group);
     __syncthreads();
   }

@@ -508,7 +508,7 @@ std::array<size_t, kPlanBuffers> plan_buffer_bytes(int64_t N, int p, int M, int 
           n * sizeof(int),                                    // slot
           2 * ncell3 * sizeof(int),                           // ccnt (two sets)
           ncell3 * cap * sizeof(double4),                     // cgrid
-          ncell3 * cap * sizeof(int),                         // cidx
+          ncell3 * cap * sizeof(float4),                      // cpre
           n * 3 * sizeof(unsigned long long),                 // freal
           n * 2 * sizeof(unsigned long long),                 // ereal
           nblk * 2 * sizeof(long long),                       // blk_er
@@ -639,7 +639,7 @@ ComputeBuffers carve_buffers(void *const *ptr) {
   b.slot = (int *)ptr[5];
   b.ccnt = (int *)ptr[6];
   b.cgrid = (double4 *)ptr[7];
-  b.cidx = (int *)ptr[8];
+  b.cpre = (float4 *)ptr[8];
   b.freal = (unsigned long long *)ptr[9];
   b.ereal = (unsigned long long *)ptr[10];
   b.blk_er = (long long *)ptr[11];
@@ -881,7 +881,7 @@ static int compute_impl(enuf_plan *plan, const double *pos, const double *q, dou
     if (e == hipSuccess) e = hipEventRecord(plan->fork_ev, st);
     if (e == hipSuccess) e = launch_recip(c, plan->buf, c.N, st, nullptr);
     if (e == hipSuccess) e = hipStreamWaitEvent(plan->side, plan->fork_ev, 0);
-    if (e == hipSuccess) e = launch_real(c, plan->buf, c.N, 1, plan->side, nullptr);
+    if (e == hipSuccess) e = launch_real(c, plan->buf, c.N, eval_scan(c), 1, plan->side, nullptr);
     if (e == hipSuccess) e = hipEventRecord(plan->join_ev, plan->side);
     if (e == hipSuccess) e = hipStreamWaitEvent(st, plan->join_ev, 0);
     if (e == hipSuccess) e = launch_combine(c, plan->buf, forces, energy, energy5, FinishArgs(), st, nullptr);
@@ -1046,7 +1046,11 @@ extern "C" int enuf_compute_noalloc(int64_t N, double box, double alpha, int p, 
     set_error("mesh too large for the LDS in this precision");
     return ENUF_EINVAL;
   }
-  const std::array<size_t, kPlanBuffers> sz = plan_buffer_bytes(N, p, M, Kc, g);
+  std::array<size_t, kPlanBuffers> sz = plan_buffer_bytes(N, p, M, Kc, g);
+  // The scratch holds the cell slots' indices; their FP32 copies, which only the
+  // real-space kernel reads, go to a buffer that the mesh passes fill after it.
+  const size_t copies = sz[8];
+  sz[8] = copies / sizeof(float4) * sizeof(int);
   const size_t need = arena_bytes(sz.data(), kPlanBuffers);
   if (need > kScratchBytes) {
     set_error("these sizes need " + std::to_string(need) + " bytes of scratch; the static scratch holds " +
@@ -1062,7 +1066,9 @@ extern "C" int enuf_compute_noalloc(int64_t N, double box, double alpha, int p, 
     ptr[k] = (char *)base + off;
     off += arena_slot(sz[k]);
   }
-  const ComputeBuffers buf = carve_buffers(ptr);
+  ComputeBuffers buf = carve_buffers(ptr);
+  buf.cidx = (int *)buf.cpre;
+  buf.cpre = sz[15] >= copies ? (float4 *)buf.part : (sz[12] >= copies ? (float4 *)buf.gzy : nullptr);
   hipStream_t st = (hipStream_t)hip_stream;
   // the previous call's contents: clear what the kernels expect to start at zero
   void *zp[8];
@@ -1334,7 +1340,7 @@ enuf_dpd *enuf_dpd_create(int64_t N, double box, const enuf_dpd_params *prm, enu
     ch.slot = plan->buf.slot;
     ch.ccnt = plan->buf.ccnt;
     ch.cgrid = plan->buf.cgrid;
-    ch.cidx = plan->buf.cidx;
+    ch.cpre = plan->buf.cpre;
     ch.cells = plan->cfg.cells;
     ch.freal = plan->buf.freal;
     ch.ereal = plan->buf.ereal;
@@ -1345,7 +1351,7 @@ enuf_dpd *enuf_dpd_create(int64_t N, double box, const enuf_dpd_params *prm, enu
     ch.m_over_l = plan->cfg.mesh.m_over_l;
     ch.sc = plan->buf.sc;
     ch.stat = st;
-    ch.stat.split = real_split(nq, plan->cfg.cells.ncell, kRealDpdBlocks);
+    ch.stat.split = real_split(nq, plan->cfg.cells.ncell, kRealDpdBlocks, kRealDpdBlocks);
   }
   if (hipStreamCreateWithFlags(&d->side, hipStreamNonBlocking) != hipSuccess ||
       hipEventCreateWithFlags(&d->join_ev, hipEventDisableTiming) != hipSuccess ||
@@ -1478,10 +1484,10 @@ static int dpd_eval(enuf_dpd *d, int mode, double *pos, double *vel, double *for
       if (e == hipSuccess)
         e = launch_dpd_pair(N, d->P, step, pos, dcnt, d->cpos, d->cvel, d->bond_start, d->bond_to,
                             d->fdpd, s1, tm, step_dev);
-      if (e == hipSuccess) e = launch_real(pl->cfg, bk, d->nq, energies ? 1 : 0, s1, tm);
+      if (e == hipSuccess) e = launch_real(pl->cfg, bk, d->nq, d->charges.stat.split.wave, energies ? 1 : 0, s1, tm);
     } else if (e == hipSuccess) {
       e = launch_dpd_pair_real(d->P, step, pos, dcnt, d->cpos, d->cvel, d->bond_start, d->bond_to, d->fdpd,
-                               pl->cfg, bk, d->nq, energies ? 1 : 0, s1, step_dev);
+                               pl->cfg, bk, d->nq, d->charges.stat.split.wave, energies ? 1 : 0, s1, step_dev);
     }
     if (events && e == hipSuccess) e = hipEventRecord(d->join_ev, s1);
     if (events && e == hipSuccess) e = hipStreamWaitEvent(st, d->join_ev, 0);
@@ -1761,6 +1767,7 @@ struct enuf_batch {
   int concurrent = 1;
   int use_graph = 1;
   int ik = -1;       // force mode of the members (all alike; -1 while empty)
+  int real_scan = kRealAny;  // the members' real-space scan, if they all take one
   int p4 = 0;        // mesh_win8 of every member (4), of none (0) or of some (-1)
   std::vector<Member> members;
   int next_id = 0;
@@ -1828,7 +1835,9 @@ namespace {
 
 // The member as table par sees it: bin-count set par (and the other set as
 // the next step's, for the fused combine + pre kernel).
-BatchMember member_view(const enuf_batch::Member &mb, const enuf_batch::Tuning &t, int par) {
+// real_target: real-space blocks to aim for (the member's part of the device).
+BatchMember member_view(const enuf_batch::Member &mb, const enuf_batch::Tuning &t, int real_target, int wave_target,
+                        int par) {
   const enuf_dpd *d = mb.d;
   const enuf_plan *pl = d->plan;
   BatchMember m{};
@@ -1841,9 +1850,8 @@ BatchMember member_view(const enuf_batch::Member &mb, const enuf_batch::Tuning &
   // is kept per line, so the grouping does not change it)
   m.cfg.mesh.xsplit = std::min(m.cfg.mesh.Kc, m.cfg.mesh.xsplit * t.x_split_mul);
   m.buf = plan_buffers_set(pl, par);
-  m.nq = (int)d->nq;
   m.nblk = pl->cfg.nblk;
-  m.real_blocks = real_blocks(pl->cfg.cells, d->nq, 0);
+  m.real_blocks = real_blocks(pl->cfg.cells, d->nq, real_target, wave_target);
   m.fscale = pl->cfg.mesh.ik ? 2.0 / (pl->cfg.L * pl->cfg.L) : (double)pl->cfg.mesh.M / (M_PI * pl->cfg.L * pl->cfg.L);
   m.inv2piL = 1.0 / (2.0 * M_PI * pl->cfg.L);
   m.N = d->N;
@@ -1867,7 +1875,7 @@ BatchMember member_view(const enuf_batch::Member &mb, const enuf_batch::Tuning &
   m.status = d->status;
   m.ch = dpd_charges_set(d, par);
   m.ch_next = dpd_charges_set(d, par ^ 1);
-  m.ch.stat.split = m.ch_next.stat.split = real_split((int)d->nq, pl->cfg.cells.ncell, 0);
+  m.ch.stat.split = m.ch_next.stat.split = real_split((int)d->nq, pl->cfg.cells.ncell, real_target, wave_target);
   m.step = d->step_ctr;
   return m;
 }
@@ -1883,12 +1891,13 @@ int batch_rebuild(enuf_batch *b) {
   std::vector<int2> map[7];
   size_t lf = 0, lx = 0, lb = 0;
   int tp = b->tune.pass_threads, tx = b->tune.x_threads;  // enough threads for every member's FFT passes
-  int n4 = 0;
+  int n4 = 0, nwave = 0;
+  const int real_target = 0, wave_target = 0;
   for (int k : order) {
-    const BatchMember m = member_view(b->members[k], b->tune, 0);
+    const BatchMember m = member_view(b->members[k], b->tune, real_target, wave_target, 0);
     const int id = (int)mem.size();
     mem.push_back(m);
-    mem1.push_back(member_view(b->members[k], b->tune, 1));
+    mem1.push_back(member_view(b->members[k], b->tune, real_target, wave_target, 1));
     const int planes = m.cfg.mesh.M * m.cfg.mesh.parts;     // work-groups of the spread pass
     const int bplanes = m.cfg.mesh.M * m.cfg.mesh.bparts;   // and of the gather pass
     const int counts[7] = {m.nblk,  m.pair_blocks, m.real_blocks, planes, m.cfg.mesh.nky * m.cfg.mesh.xsplit,
@@ -1896,6 +1905,7 @@ int batch_rebuild(enuf_batch *b) {
     for (int s = 0; s < 7; ++s)
       for (int i = 0; i < counts[s]; ++i) map[s].push_back(make_int2(id, i));
     n4 += mesh_win8(m.cfg.mesh) ? 1 : 0;
+    nwave += m.ch.stat.split.wave;
     lf = std::max(lf, m.cfg.lds_fwd);
     lx = std::max(lx, m.cfg.lds_x);
     lb = std::max(lb, m.cfg.lds_bwd);
@@ -1948,6 +1958,7 @@ int batch_rebuild(enuf_batch *b) {
   b->lds_fwd = lf;
   b->lds_x = lx;
   b->lds_bwd = lb;
+  b->real_scan = nwave == (int)order.size() ? kRealWave : (nwave == 0 ? kRealSegment : kRealAny);
   b->p4 = n4 == (int)order.size() ? 4 : (n4 == 0 ? 0 : -1);
   b->pass_threads = tp;
   b->x_threads = tx;
@@ -1979,7 +1990,7 @@ hipError_t batch_forces(enuf_batch *b, const BatchMember *mt, bool fork, int ene
   if (tm) tm->after(ENUF_K_DPD_PAIR, s0);
   if (fork && e == hipSuccess) e = hipEventRecord(b->join_ev[0], s0);
   if (tm) tm->before(ENUF_K_REAL, s1);
-  if (e == hipSuccess) e = launch_batch_real(mt, mp + o[2], o[3] - o[2], energies, s1);
+  if (e == hipSuccess) e = launch_batch_real(mt, mp + o[2], o[3] - o[2], b->real_scan, energies, s1);
   if (tm) tm->after(ENUF_K_REAL, s1);
   if (fork && e == hipSuccess) e = hipEventRecord(b->join_ev[1], s1);
   if (e == hipSuccess)
