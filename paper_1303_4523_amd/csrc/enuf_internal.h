@@ -36,7 +36,8 @@ constexpr int kMaxParts = 8;       // most work-groups per plane in the spread a
 // `blocks` is the number of blocks to ask for: kRealTargetBlocks for a single
 // evaluation; kRealDpdBlocks for a DPD step, where the pair kernel and the mesh
 // passes share the device (642 against 678 us per 11 steps at N = 3333, the same
-// at N = 24000); none for batches, which fill the device.
+// at N = 24000); none for batches that fill the device; for others an equal part
+// of kRealTargetBlocks each.
 // Staging pays where a cell's charges share it: 24000 charges, 6 per cell, 36 us
 // a launch against 52 by wavefronts, 47 per cell 121 against 137.  With fewer
 // than 2 per cell the 27 cells hold less than a block's lanes (24000 charges on
@@ -54,6 +55,10 @@ constexpr int kRealThreads = 256;
 constexpr int kRealOwn = 64;
 constexpr int kRealSegMax = 4;
 constexpr int kRealTargetBlocks = 512, kRealDpdBlocks = 216;
+// A batch fills the device's real-space kernel above either (1 dense member of
+// 1500 particles: 1183 us per 6 replayed steps with no target, 693 with it; 8
+// sparse ones, 9000 charges: 912 and 920).
+constexpr int kRealBatchCharges = 10000, kRealBatchMembers = 5;
 constexpr int kRealStage = 384;  // candidates staged at a time
 constexpr int kRealFill = 336;   // staged candidates a segment may expect
 constexpr int kRealWaveBlocks = 2048;  // most blocks of the wavefront-per-charge scan

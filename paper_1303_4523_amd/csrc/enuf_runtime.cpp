@@ -1892,7 +1892,10 @@ int batch_rebuild(enuf_batch *b) {
   size_t lf = 0, lx = 0, lb = 0;
   int tp = b->tune.pass_threads, tx = b->tune.x_threads;  // enough threads for every member's FFT passes
   int n4 = 0, nwave = 0;
-  const int real_target = 0, wave_target = 0;
+  int64_t charges = 0;
+  for (int k : order) charges += b->members[k].d->nq;
+  const bool few = charges <= kRealBatchCharges && !order.empty() && order.size() <= (size_t)kRealBatchMembers;
+  const int real_target = few ? kRealTargetBlocks / (int)order.size() : 0, wave_target = few ? kRealTargetBlocks : 0;
   for (int k : order) {
     const BatchMember m = member_view(b->members[k], b->tune, real_target, wave_target, 0);
     const int id = (int)mem.size();

@@ -1,7 +1,8 @@
 """The work split of the real-space kernel (host rule, compiled with g++).
 
 Which of the two scans a system gets, and how many work-groups: a work-group of
-four wavefronts per charge (grids with far more cells than charges) and a share's whole neighbourhood staged for a
+four wavefronts per charge (grids with far more cells than charges), few blocks
+for the one member of a batch, and a share's whole neighbourhood staged for a
 handful of charges were all slower than a wavefront per charge.
 """
 import os
@@ -22,7 +23,7 @@ using namespace enuf;
 #define CHECK(x) do { if (!(x)) { std::printf("line %d: %s (n %d nq %d blocks %d)\n", __LINE__, #x, n, nq, blocks); \
                                   std::exit(1); } } while (0)
 int main() {
-  for (int blocks : {0, 100, kRealDpdBlocks, kRealTargetBlocks})
+  for (int blocks : {0, kRealTargetBlocks / kRealBatchMembers, kRealDpdBlocks, kRealTargetBlocks})
     for (int n = 1; n <= 40; ++n) {
       bool wave = true;
       for (int nq = 0; nq <= 300 * n * n * n && nq <= 400000; nq += 1 + nq / 40) {
