@@ -174,7 +174,7 @@ struct MeshParams {
 // wrapping along z.
 constexpr int mesh_stride(int M, int p) { return p == 4 ? M + 7 : M + 1; }
 
-// Whether the kernels of half-width 4 run (the LDS budget admits their rows).
+// Whether the kernels of half-width 4 run (mesh_choose_rows took their rows).
 constexpr bool mesh_win8(const MeshParams &m) { return m.win.p == 4 && m.Mp == mesh_stride(m.M, 4); }
 
 // Entries of the window tables: value and derivative series [2][2p][D + 1]

@@ -1483,13 +1483,28 @@ static bool choose_rows(MeshParams &m, int precision, size_t max_lds) {
   return false;
 }
 
+// The kernels of half-width 4 take rows that are 6 longer, beside which fewer
+// charges may be staged.  They give a charge 4 lanes at most and so leave threads
+// idle on batches below 128 charges, the general ones (8 lanes) below 64: where
+// the longer rows halve a stage of this size, or leave less, the general kernels
+// are faster (9600 charges; general and half-width 4, us an evaluation; M = 160,
+// Kc = 40: 459 and 618 at a stage of 64 and 32 in FP64, 251 and 311 at 128 and
+// 64 in mixed; M = 256, Kc = 32, mixed: 465 and 792 at 64 and 32; M = 180, Kc =
+// 22, FP64: 321 and 336 at 128 and 64; M = 128, Kc = 16, mixed: 124 and 133 at 256
+// and 128).  The windows weigh more in FP64 (M = 120, Kc = 15: 162 and 143 at 256
+// and 128; M = 250, Kc = 31: 1116 and 1083 at 64 both, against 904 and 1230 in
+// mixed at Kc = 62), so there the line lies a step lower.  More chunks of rows
+// cost less than a small stage (M = 160, Kc = 20, FP64: 278 us at 2 chunks and 64,
+// 196 at 3 and 512).  Never more slots for the gather's partials (memory).
 bool mesh_choose_rows(MeshParams &m, int precision, size_t max_lds) {
-  m.Mp = mesh_stride(m.M, m.win.p);
-  if (choose_rows(m, precision, max_lds)) return true;
-  // an LDS budget that only the general kernels' narrower rows meet
-  if (m.Mp == m.M + 1) return false;
   m.Mp = m.M + 1;
-  return choose_rows(m, precision, max_lds);
+  if (!choose_rows(m, precision, max_lds)) return false;
+  MeshParams w = m;
+  w.Mp = mesh_stride(m.M, m.win.p);
+  if (w.Mp == m.Mp || !choose_rows(w, precision, max_lds) || w.nslot > m.nslot) return true;
+  const int s = precision == 0 ? 64 : 128;
+  if (w.stage >= 2 * s || (w.stage >= s && m.stage <= s)) m = w;
+  return true;
 }
 
 hipError_t configure_kernels(size_t max_lds) {
