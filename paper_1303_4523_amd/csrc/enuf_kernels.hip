@@ -309,20 +309,12 @@ __device__ inline int stage_plane_commit(bool take, int j, int b, const double4 
   return *s_n;
 }
 
-// Mesh cell and fractional offset of one coordinate.
-__device__ inline int cell_frac(double x, double m_over_l, int M, double *frac) {
-  double t;
-  const int c = mesh_cell(x, m_over_l, M, &t);
-  *frac = t - (double)c;
-  return c;
-}
-
-// The same with the product's rounding stated: rounded with the difference
-// (FUSED), or before it.  The mesh passes of half-width 4 round each fraction as
-// the general ones are compiled to (all fused in the spread, y before it in the
-// gather), so that both find the same windows to the last bit.
+// Mesh cell and fractional offset of one coordinate, the product rounded with the
+// difference (FUSED) or before it.  The rounding is stated so that every mesh
+// kernel finds the same windows to the last bit (fused in the spread; y before
+// the difference in the gather), alone or in a batch and whatever its half-width.
 template <bool FUSED>
-__device__ __forceinline__ int cell_frac_as(double x, double m_over_l, int M, double *frac) {
+__device__ __forceinline__ int cell_frac(double x, double m_over_l, int M, double *frac) {
 #pragma clang fp contract(off)
   double t;
   const int c = mesh_cell(x, m_over_l, M, &t);
@@ -478,9 +470,9 @@ __device__ __forceinline__ void spread8(const MeshParams &mp, ctab<T> tab, const
   for (int e = threadIdx.x / L; e < cnt; e += blockDim.x / L) {
     const double4 c = s_c[e];
     double fx, fy, fz;
-    cell_frac_as<true>(c.x, mp.m_over_l, M, &fx);
-    const int cy = cell_frac_as<true>(c.y, mp.m_over_l, M, &fy);
-    const int cz = cell_frac_as<true>(c.z, mp.m_over_l, M, &fz);
+    cell_frac<true>(c.x, mp.m_over_l, M, &fx);
+    const int cy = cell_frac<true>(c.y, mp.m_over_l, M, &fy);
+    const int cz = cell_frac<true>(c.z, mp.m_over_l, M, &fz);
     const T x[2] = {(T)(2.0 * fz - 1.0), (T)(2.0 * fy - 1.0)}, ux[1] = {(T)(2.0 * fx - 1.0)};
     T w[2][8], none[2][8], wx[1];
     window8<2, false>(tab, D, x, w, none);
@@ -588,9 +580,9 @@ recip_fwd_body(gptr<const double4> __restrict__ xq, gptr<const int> __restrict__
         const int b = s_jb[2 * e + 1];
         const double4 c = s_c[e];
         double fx, fy, fz;
-        cell_frac(c.x, mp.m_over_l, M, &fx);
-        const int cy = cell_frac(c.y, mp.m_over_l, M, &fy);
-        const int cz = cell_frac(c.z, mp.m_over_l, M, &fz);
+        cell_frac<true>(c.x, mp.m_over_l, M, &fx);
+        const int cy = cell_frac<true>(c.y, mp.m_over_l, M, &fy);
+        const int cz = cell_frac<true>(c.z, mp.m_over_l, M, &fz);
         if (act) {
           const int sx = P2 - 1 - b;
           const T *const ser[3] = {cv + sy * Ds, cv + sx * Ds, cv + sy * Ds};
@@ -837,9 +829,9 @@ __device__ __forceinline__ void gather8(const MeshParams &mp, ctab<T> tab, const
     const double4 c = s_c[e];
     const int j = s_jb[2 * e], sx = 7 - s_jb[2 * e + 1];
     double fx, fy, fz;
-    cell_frac_as<true>(c.x, mp.m_over_l, M, &fx);
-    const int cy = cell_frac_as<false>(c.y, mp.m_over_l, M, &fy);
-    const int cz = cell_frac_as<true>(c.z, mp.m_over_l, M, &fz);
+    cell_frac<true>(c.x, mp.m_over_l, M, &fx);
+    const int cy = cell_frac<false>(c.y, mp.m_over_l, M, &fy);
+    const int cz = cell_frac<true>(c.z, mp.m_over_l, M, &fz);
     const T x[2] = {(T)(2.0 * fz - 1.0), (T)(2.0 * fy - 1.0)}, ux = (T)(2.0 * fx - 1.0);
     T w[2][8], d[2][8], wx, dwx = (T)0;
     window8<2, !IK>(tab, D, x, w, d);
@@ -1074,9 +1066,9 @@ recip_bwd_body(gptr<const double4> __restrict__ xq, gptr<const int> __restrict__
           sx = P2 - 1 - s_jb[2 * e + 1];
           const double4 c = s_c[e];
           double fx, fy, fz;
-          cell_frac(c.x, mp.m_over_l, M, &fx);
-          cy = cell_frac(c.y, mp.m_over_l, M, &fy);
-          const int cz = cell_frac(c.z, mp.m_over_l, M, &fz);
+          cell_frac<true>(c.x, mp.m_over_l, M, &fx);
+          cy = cell_frac<false>(c.y, mp.m_over_l, M, &fy);
+          const int cz = cell_frac<true>(c.z, mp.m_over_l, M, &fz);
           if (act) {
             const T ux = (T)(2.0 * fx - 1.0), uy = (T)(2.0 * fy - 1.0), uz = (T)(2.0 * fz - 1.0);
             if (IK) {
