@@ -635,7 +635,7 @@ k_dpd_pair(DpdParams P, uint64_t step, const unsigned long long *step_dev, const
 // `real.blocks` work-groups: both need only the pre kernel's bins, and as
 // launches of their own the second one's start, its few work-groups and its
 // tail came after the first, on the longest path of a small step (20 steps of
-// 24000 particles 1383 -> 1165 us, 11 of 3333 particles 647 -> 616 us).  The
+// 24000 particles 1383 -> 1198 us, 11 of 3333 particles 647 -> 625 us).  The
 // real-space work-groups use the pair stage's LDS.
 struct RealArgs {
   const double4 *xq;

@@ -18,9 +18,10 @@ constexpr int kMaxRadixPasses = 16;
 constexpr int kMaxChebDeg = 24;    // highest degree of the window series
 constexpr int kStage = 512;        // most charges of a plane staged in LDS at a time by the mesh passes
 // Batched mesh passes: work-groups of kBatchPassThreads threads staging at most
-// kBatchStage charges, so that two work-groups share a CU (the passes need
-// about 200-256 VGPRs per lane, two waves per SIMD): one work-group's waits on
-// memory and barriers overlap the other's work.
+// kBatchStage charges, so that several share a CU's LDS and registers (74-160
+// VGPRs per lane, three to six waves per SIMD): one work-group's waits on memory
+// and barriers overlap the others' work.  (Chosen when the passes needed 200-256
+// VGPRs and 512 threads filled a CU; not chosen again since.)
 constexpr int kBatchPassThreads = 256;
 constexpr int kBatchStage = 256;
 // The batched x pass (no charges, little LDS) in work-groups of 128 threads:

@@ -113,8 +113,10 @@ __device__ __forceinline__ double fma_sc(double a, double b, double c) {
   return d;
 }
 
-// e^x for x <= 0 (0 below -745): reduction by ln 2 in two parts, the Taylor
-// polynomial of degree 13 on |r| <= ln 2 / 2 (remainder below 5e-18).
+// e^x for x <= 0 (0 below -745): reduction by ln 2 in two parts, its leading 33
+// bits (times k < 2^11 exact) and the rest (W. J. Cody and W. Waite, Software
+// Manual for the Elementary Functions, 1980), and the Taylor polynomial of degree
+// 13 on |r| <= ln 2 / 2 (remainder below 5e-18).
 __device__ __forceinline__ double exp_f64(double x) {
 #pragma clang fp contract(off)
   const cptr c = pair_coef(kOffExp);
@@ -366,7 +368,8 @@ __device__ __forceinline__ double real_factor(double r, double a, double lam) {
   return ff;
 }
 
-// The polynomials and the library agree to kRealSlack of |qq| / r^2.  A force
+// The polynomials and the library agree to kRealSlack of |qq| / r^2 (checked
+// against the C library's functions, over each range of alpha r_cut).  A force
 // term whose rounding to fixed point that much could change (one pair in
 // several hundred), or that is too large for real_add, is left to real_redo,
 // which takes the library's value: the rounded terms, and so whole
