@@ -308,11 +308,14 @@ struct RealShared {
 // A lane's running sum of terms rounded to multiples of 1 / kRealFxScale: v x
 // kRealFxScale + 1.5 x 2^52 rounds to an integer (ulp 1), and sums of integers
 // below 2^53 are exact in FP64.  A charge's sum over a window has at most
-// kRealStage terms; those of 2^42 (a force of 64) or more go to the int64 sum
-// directly.
+// kRealStage terms, so those below 2^44 (a force of 256) are summed here and
+// those of 2^44 or more go to the int64 sum by real_redo.  (With a line at 2^42, the
+// most that a conversion by real_add's trick allows, 43 % of the pairs of charges
+// of 18.2 -- kcal/mol and Angstrom -- went there: the kernel at 24000
+// particles, 70 % of them charged, 274 us; 206 with this line, 164 for charges of 1.)
 constexpr double kRealMagic = 6755399441055744.0;  // 1.5 x 2^52
-constexpr double kRealSmall = 4398046511104.0;     // 2^42
-static_assert(kRealStage <= 512, "sums below 2^51");
+constexpr double kRealSmall = 17592186044416.0;    // 2^44
+static_assert(kRealStage <= 512, "sums below 2^53");
 __device__ __forceinline__ void real_add(double &sum, double v) {
 #pragma clang fp contract(off)
   sum += (v * kRealFxScale + kRealMagic) - kRealMagic;
@@ -325,7 +328,7 @@ __device__ __forceinline__ double real_round(double v, double *moved) {
   return k;
 }
 __device__ __forceinline__ unsigned long long real_sum(double sum) {
-  return (unsigned long long)(__double_as_longlong(sum + kRealMagic) - __double_as_longlong(kRealMagic));
+  return (unsigned long long)(long long)sum;
 }
 
 // Squared radius of the FP32 pre-test: r_cut plus 8 FP32 ulps of the box
