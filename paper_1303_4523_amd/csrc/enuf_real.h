@@ -372,10 +372,12 @@ __device__ __forceinline__ double real_factor(double r, double a, double lam) {
 }
 
 // The polynomials and the library agree to kRealSlack of |qq| / r^2 (checked
-// against the C library's functions, over each range of alpha r_cut).  A force
-// term whose rounding to fixed point that much could change (one pair in
-// several hundred), or that is too large for real_add, is left to real_redo,
-// which takes the library's value: the rounded terms, and so whole
+// against the C library's functions, over each range of alpha r_cut; largest
+// difference on the device, 2 x 10^8 distances in each of 22 sets of alpha, r_cut
+// and lambda: 2^-49.1).  A force term whose rounding to fixed point that much could
+// change (one pair in several hundred for charges of 1; in proportion to |qq|, so
+// most pairs from charges of 50 on), or that is too large for real_add, is left to
+// real_redo, which takes the library's value: the rounded terms, and so whole
 // trajectories, are those of the library's functions.  Measured: 60001 particles,
 // 70 % of them charged, divalent ions: 301 us an evaluation, 288 without the
 // second evaluation, 388 with the library's functions for all pairs; listing
